@@ -116,6 +116,11 @@ __host__ __device__ inline dd pval_dd(double d) {
 // the host each is an ordinary division.
 //   recip_est: the bare estimate, where only a sign is used;
 //   recip1:    one step, where a following correction absorbs the error;
+//   recip3:    one third-order step, r (1 + e + e^2) with e = 1 - x r: the error
+//              e^3 is below 2^-70, so the result is the correctly rounded one but
+//              where 1/x lies within 2^-17 ulp of a rounding boundary.  The rational
+//              passes' reciprocal: bound by issued instructions, it takes 3 FMAs
+//              after the estimate where two Newton steps take 4;
 //   recip:     two steps, everywhere else.
 __host__ __device__ inline double recip_est(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -129,6 +134,16 @@ __host__ __device__ inline double recip1(double x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const double r = __builtin_amdgcn_rcp(x);
   return fma(r, fma(-x, r, 1.0), r);
+#else
+  return 1.0 / x;
+#endif
+}
+
+__host__ __device__ inline double recip3(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 #else
   return 1.0 / x;
 #endif
@@ -389,7 +404,7 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
       if constexpr (ord == 1) e = dd{ej, (-di) - (ej - t.d)};
       else if constexpr (ord == 2) e = dd{ej, t.d - (ej + di)};
       else e = pdiff_dd<KIND>(t.d, di);
-      if (above) dd_acc_div2(p2, dd{t.ch, t.cl}, e, rj); else dd_acc_div2(p1, dd{t.ch, t.cl}, e, rj);
+      if (above) dd_acc_div2<false>(p2, dd{t.ch, t.cl}, e, rj); else dd_acc_div2<true>(p1, dd{t.ch, t.cl}, e, rj);
     }
     // zeta_j^2 (gs / e_j)^2 = w gs and zeta_j^2 (gs / e_j)^3 = w (gs / e_j) gs with
     // w = (zeta_j^2 / e_j)(gs / e_j) <= |zeta_j^2 / e_j|: the factor gs is applied
@@ -611,7 +626,7 @@ __host__ __device__ inline void psi_pass(const Prob& P, double pv, double s, int
   double a = 0.0, b = 0.0, c = 0.0;
   for_terms_ld<G>(ln, P.m, excl, [&](int j) { return v2{P.ds[j], P.ch[j]}; }, [&](int, bool, const v2& t) {
     const double e = OFF ? pdiff<KIND>(t.a, pv) - s : pdiff<KIND>(t.a, pv);
-    const double q = recip(e * fma(nu, e, -1.0));
+    const double q = recip3(e * fma(nu, e, -1.0));
     const double v = e * q;                // 1 / (nu e - 1)
     a = fma(t.b, q, a);
     const double d1 = (t.b * v) * v;
