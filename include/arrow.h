@@ -333,17 +333,17 @@ int arrow_set_lanes_table(arrow_handle_t h, int scope, int32_t entries, const in
  * Diagnostics of the most recent single-problem call on this handle.
  *
  * arrow_last_timing: ms[0..4] receive the elapsed times (milliseconds, from
- *   HIP events on the handle's stream) of the stages front (sortedness check;
- *   for input already in decreasing order also the copy and the shaft weights
- *   and corner), sort (input not in that order: rank sort, copy, weights and
- *   corner), root (shift, b, root of the inverse), check (K_nu, repairs, norm)
- *   and vectors.  The events are stamped by the kernels' own dispatches (no
- *   marker packets between launches): root and vectors are their kernels'
- *   durations, front and sort run from one kernel's start to the next one's,
- *   check from the end of the root kernel to the start of the vector kernel,
- *   so the five sum to the whole call.  Needs ARROW_OPT_TIMING set before that
- *   call; waits for it to finish.  Returns ARROW_ERR_STATE when no timed call
- *   exists.
+ *   HIP events on the handle's stream) of the stages front (order check, copy,
+ *   shaft weights and corner; up to 16384 poles the rank sort too), sort (above
+ *   that: the rank sort of input not in order, with the weights and corner),
+ *   root (shift, b, root of the inverse), check (K_nu, repairs, norm) and vectors.
+ *   The events are stamped by the kernels' own dispatches (no marker packets
+ *   between launches): front (up to 16384 poles), root and vectors are their
+ *   kernels' durations, sort and check the time between them.  Up to n = 1280 one
+ *   kernel does check and vectors, and counts as vectors; without vectors, the
+ *   last kernel of the check does.  The five sum to the call up to the end of that
+ *   kernel.  Needs ARROW_OPT_TIMING set before that call; waits for it to finish.
+ *   Returns ARROW_ERR_STATE when no timed call exists.
  * arrow_timing_of: the same for the most recent timed call (age 0) or the one
  *   before it (age 1): the handle keeps the stage events of two timed calls, so
  *   a caller can read a call's stages after queuing the next one without

@@ -1,20 +1,20 @@
 // libarrow: gfx950 kernels and the C ABI declared in include/arrow.h.
 //
 // One call runs these launches on the handle's stream:
-//   k_front     sortedness check; for sorted input also the copy to the
-//               workspace and the prologue: shaft weights and corner of the
-//               (reduced) arrowhead in double-double, and the deflation of a
-//               reducible arrowhead (Sec. 1)
-//   k_sort      unsorted input only: rank of every pole (symmetric permutation
-//               to decreasing order, Sec. 1), the permuted copy, the prologue
+//   k_prep      rank of every pole (symmetric permutation to decreasing order,
+//               Sec. 1), the permuted copy and the prologue: shaft weights and
+//               corner of the (reduced) arrowhead in double-double, and the
+//               deflation of a reducible arrowhead (Sec. 1).  Above PREP_MAX poles
+//               k_front (order check; for ordered input all of that) and k_sort
+//               (the rank count of unordered input) take its place
 //   k_root      per eigenvalue: shift selection, b, root of the inverse (Algorithms 1-3, Theorem 6)
-//   k_check     per eigenvalue: K_nu test (Algorithm 5), norm; repairs are deferred
-//   k_repair    the deferred repairs (Remarks 1-2, DPR1 re-measure), a block per eigenvalue;
-//               then the eigenpairs a reducible arrowhead deflated (Sec. 1) are placed
-//   k_vec       eigenvector entries, streamed to HBM (eq. eigenvecAi, Algorithm 4);
-//               k_vec_c the complex ones of a Hermitian arrowhead (Sec. 6.1)
-// k_root / k_check give G lanes of a wavefront to each eigenvalue (G = 64: one
-// wavefront per eigenvalue); k_vec is bound by the n^2 FP64 stores.
+//   k_finish    per eigenvalue: K_nu test (Algorithm 5), repairs (Remarks 1-2, DPR1
+//               re-measure), norm, then its eigenvector, streamed to HBM
+//               (eq. eigenvecAi, Algorithm 4; complex for a Hermitian arrowhead, Sec. 6.1).
+//               Above FIN_MAX k_check, k_repair and k_vec take its place
+//   k_defl      arrowheads only: the eigenpairs a reducible one deflated (Sec. 1)
+// k_root gives G lanes of a wavefront to each eigenvalue (G = 64: one
+// wavefront per eigenvalue); the vectors are bound by the n^2 FP64 stores.
 
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -25,6 +25,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <type_traits>
 
 #include "../../include/arrow.h"
 #include "blocks.hpp"
@@ -48,11 +49,144 @@ static_assert(ARROW_INFO_DD_B == INFO_DD_B && ARROW_INFO_REMEDY_A == INFO_REMEDY
 // ---------------------------------------------------------------------------
 // kernels
 
-// Sorting (symmetric permutation to decreasing poles, Sec. 1): a one-block
-// check whether the input already is in that order, or in the reverse one
-// (the usual cases), then, only if not, a rank count over a 2-D grid of (pole
-// tile, comparison chunk) blocks, then the scatter.  rank[] holds the count
-// in its low 30 bits and a duplicate marker in bit 30.
+// Sorting (symmetric permutation to decreasing poles, Sec. 1) and the prologue,
+// up to PREP_MAX poles, in one launch.  Every block asks whether the input already
+// is in that order, or in the reverse one (the usual cases); only if not, a pole's
+// rank is counted: a wavefront holds 64 keys, one a lane, and reads the keys it
+// compares them with through the scalar cache (the same for all lanes), the next
+// 16 under way while it compares, two instructions a comparison; the block's
+// wavefronts share the keys out.  The thread that has the rank writes the sorted
+// entry and its weight, and the last block to finish (the only one up to PREP_ONE
+// poles) reduces the statuses and the corner.  Bound by latency (a chain of
+// dependent loads and one pass through the device-scope release and acquire).
+// An order check in one block and a rank count whose last block scattered
+// everything took 33 us at n = 199 shuffled, 44 us at 1025, 56 us at 2047 (ordered:
+// 6.5 us at 512, 13.6 us at 4096); this 11, 12 and 24 us (7.6 and 9.3 us).
+constexpr int PREP_BLOCK = 1024;
+constexpr int PREP_WAVES = PREP_BLOCK / 64;
+constexpr int PREP_ONE = 256;     // poles one block ranks alone: 64 comparisons a lane
+constexpr int PREP_MAX = 16384;   // the blocks' order checks read n^2 / 64 keys from the L2
+constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (its rank is none)
+
+__host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
+
+template <int KIND, bool ONE>
+__global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* __restrict__ poles, int groups) {
+  __shared__ int part[PREP_WAVES][64];
+  __shared__ double least[PREP_WAVES];
+  __shared__ int last;
+  const Ws w = ws_view(D.ws, D.n);
+  const int ms = sorted_count(D), m = D.n - 1;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // `groups` groups of 64 keys a block, PREP_WAVES / groups wavefronts each
+  const int grp = wave % groups, share = wave / groups, shares = PREP_WAVES / groups;
+  const int j0 = (blockIdx.x * groups + grp) * 64, j = j0 + lane;
+  auto key = [&](double d) { return sort_key<KIND>((KIND == KIND_DPR1 && D.neg) ? -d : d); };
+  // this lane's entry
+  constexpr int S = (KIND == KIND_HERM) ? 2 : 1;
+  const bool has = share == 0 && j < ms;
+  const double dj = (j < ms) ? poles[j] : NAN, kj = key(dj);
+  const double re = has ? D.z[S * j] : 0.0, im = (KIND == KIND_HERM && has) ? D.z[S * j + 1] : 0.0;
+  double dn = INFINITY;   // DPR1: the last sorted pole
+  int down = 0, up = 0;   // some pair not strictly decreasing / not strictly increasing
+  for (int q = threadIdx.x; q < ms; q += PREP_BLOCK) {
+    const double a = key(poles[q]), b = (q + 1 < ms) ? key(poles[q + 1]) : 0.0;
+    if (q + 1 < ms) {
+      if (!(a > b)) down = 1;
+      if (!(a < b)) up = 1;
+    }
+    if (KIND == KIND_DPR1) dn = fmin(dn, a);
+  }
+  if constexpr (KIND == KIND_DPR1) {
+    dn = gmin<64>(dn);
+    if (lane == 0) least[wave] = dn;
+  }
+  down = __syncthreads_or(down);
+  up = __syncthreads_or(up);
+  if constexpr (KIND == KIND_DPR1) {
+    dn = least[0];
+    for (int q = 1; q < PREP_WAVES; ++q) dn = fmin(dn, least[q]);
+  }
+  int r = down ? ms - 1 - j : j;
+  if (down && up) {
+    const int chunk = (ms + shares - 1) / shares;
+    const int l0 = min(ms, share * chunk), l1 = min(ms, l0 + chunk);
+    int cnt = 0;   // keys in front of j's: greater ones, and equal ones of smaller index
+    auto scan = [&](int a, int b, auto&& before) {
+      constexpr int N = 16;
+      int l = a;
+      if (l + N <= b) {
+        double now[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) now[u] = poles[l + u];
+        for (; l + 2 * N <= b; l += N) {
+          double next[N];
+#pragma unroll
+          for (int u = 0; u < N; ++u) next[u] = poles[l + N + u];
+#pragma unroll
+          for (int u = 0; u < N; ++u) cnt += before(key(now[u]), l + u) ? 1 : 0;
+#pragma unroll
+          for (int u = 0; u < N; ++u) now[u] = next[u];
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) cnt += before(key(now[u]), l + u) ? 1 : 0;
+        l += N;
+      }
+      for (; l < b; ++l) cnt += before(key(poles[l]), l) ? 1 : 0;
+    };
+    scan(l0, min(l1, j0), [&](double kl, int) { return kl >= kj; });
+    scan(max(l0, j0), min(l1, j0 + 64), [&](double kl, int l) { return kl > kj || (kl == kj && l < j); });
+    scan(max(l0, j0 + 64), l1, [&](double kl, int) { return kl > kj; });
+    part[wave][lane] = cnt;
+    __syncthreads();
+    r = 0;
+    for (int q = 0; q < shares; ++q) r += part[q * groups + grp][lane];
+  }
+  if (has) {   // r < ms: the other keys in front of j's
+    const SortedEntry e = put_sorted_vals<KIND>(w, r, j, (KIND == KIND_DPR1 && D.neg) ? -dj : dj, re, im);
+    w.st[j] = input_status_vals<KIND>(dj, re, im, false) | (kj == kj ? 0u : ST_NAN);
+    if (r < m) prologue_vals<KIND>(D, w, r, e.d, e.z, e.c, dn);
+  }
+  if constexpr (!ONE) {
+    // behind the barrier one thread releases the block's entries at device scope
+    // (a write-back of the L2 a wavefront, so one is enough) and counts the block
+    // in (the count wraps to 0 for the next call); the last block acquires
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      last = atomicInc(sort_done(w), gridDim.x - 1) == gridDim.x - 1;
+      if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    if (!last) return;
+  } else {
+    __syncthreads();
+  }
+  // the corner's partial sums run over the sorted entries r = t, t + PREP_BLOCK,
+  // ...: the same bits whatever the order of the input; equal poles are neighbours
+  uint32_t st = 0, zp = 0;
+  int dup = 0;
+  dd acc = {0.0, 0.0};
+  for (int r = threadIdx.x; r < ms; r += PREP_BLOCK) {
+    const double d = w.ds[r];
+    st |= w.st[r];
+    if (r + 1 < ms && sort_key<KIND>(d) == sort_key<KIND>(w.ds[r + 1])) dup = 1;
+    if (r < m && d == 0.0) zp = 1;
+    acc = dd_add(acc, corner_term<KIND>(D, w, r));
+  }
+  if (__syncthreads_or(st & ST_NAN)) {   // some slots were never written: compare the inputs themselves
+    dup = 0;
+    for (int q = threadIdx.x; q < ms; q += PREP_BLOCK)
+      for (int l = 0; l < ms; ++l) dup |= l != q && key(poles[l]) == key(poles[q]);
+  }
+  prologue_reduce<KIND, PREP_BLOCK>(D, w, acc, (st & ~ST_NAN) | (dup ? INFO_REDUCIBLE : 0u), zp);
+}
+
+// Above PREP_MAX poles: a one-block check whether the input already is in that
+// order, or in the reverse one (the usual cases), then, only if not, a rank
+// count over a 2-D grid of (pole tile, comparison chunk) blocks, then the
+// scatter.  rank[] holds the count in its low 30 bits and a duplicate marker in bit 30.
 constexpr int SORT_CHUNK = 256;   // keys of one comparison chunk
 constexpr int SORT_BLOCK = 1024;  // the last block also scatters and runs the prologue: a wide one
 
@@ -63,8 +197,6 @@ __host__ __device__ inline uint32_t* rank_array(const Ws& w, int64_t n) { return
 // prologue are done here and k_sort returns at once, else the rank array and
 // k_sort's completion counter are cleared for it.
 constexpr int FRONT_BLOCK = 1024;
-
-__host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
 
 template <int KIND>
 __global__ __launch_bounds__(FRONT_BLOCK) void k_front(ProbDesc D) {
@@ -157,6 +289,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(ProbDesc D, int chunk, int 
   __syncthreads();
   if (!last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (threadIdx.x == 0) *sort_done(w) = 0u;   // as k_prep leaves it
   for (int q = threadIdx.x; q < ms; q += SORT_BLOCK) {
     const uint32_t raw = __hip_atomic_load(&rank[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int r = (int)(raw & 0x3fffffffu);
@@ -167,7 +300,7 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(ProbDesc D, int chunk, int 
   prologue_block<KIND, SORT_BLOCK>(D);
 }
 
-// Root and check stages: ROOT_BLOCK threads per block, G lanes per
+// Root stage: ROOT_BLOCK threads per block, G lanes per
 // eigenvalue.  When the sorted poles and shaft weights fit, the block first
 // copies them to LDS and every O(n) pass reads them from there.
 constexpr int ROOT_BLOCK = 512;
@@ -208,67 +341,210 @@ __global__ __launch_bounds__(ROOT_BLOCK) void k_root(ProbDesc D, Options opt) {
   else root_body<KIND, G>(D, opt, k, (int)(gid % G));
 }
 
-template <int KIND, int G, bool STAGE>
-__global__ __launch_bounds__(ROOT_BLOCK) void k_check(ProbDesc D, Options opt) {
-  extern __shared__ double lds[];
-  if constexpr (STAGE) stage_hot(D, lds);
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // blocks of ROOT_BLOCK, or CHECK_LANE_BLOCK
-  const int k = (int)(gid / G);
-  if (k >= D.n) return;
-  if constexpr (STAGE) check_body<KIND, G, true, DEFER_ALL>(D, opt, k, (int)(gid % G), lds, lds + sorted_count(D));
-  else check_body<KIND, G, false, DEFER_ALL>(D, opt, k, (int)(gid % G));
-}
+// After the root stage: the K_nu test and the outputs of every eigenvalue, the
+// repairs of the few that need O(n) passes (check_body, DEFER_BLOCK), the vectors.
+//
+// Up to FIN_MAX, one launch (k_finish).  Column blocks take `cols` consecutive
+// eigenvalues: test and outputs, one lane each, then the columns that are final,
+// BLOCK * RPT rows at a time with the rows' data in registers.  The repairs are
+// left to the redo blocks, first in the grid: block b asks of k = b, b +
+// redo_blocks, ..., re-solves those on all its lanes from arrays staged in LDS and
+// writes their columns, so a repair's chain of passes (10 us) runs beside the
+// other blocks instead of between two launches (n = 512: 12 us against 20 us for
+// check, repair and vectors; n = 1025 complex 20 us against 23 us).
+//
+// Above, a launch each (k_check, k_repair, k_vec): the redo blocks would reserve
+// 16 n bytes of LDS in every block of the launch, and clusters of listed
+// eigenvalues need the even spread of a list that a launch boundary completes
+// (graded n = 4096: 49 us against 66 us in one launch; handing the list out
+// inside the launch by device-scope atomics 430 us).
+constexpr int FIN_MAX = 1280;
+constexpr int FIN_COLS = 32;       // most columns a block takes
+constexpr int FIN_VALUES = 64;     // eigenvalues a column block takes, without vectors
 
-// The eigenvalues k_check deferred (Remarks 1 and 2, the DPR1 re-measure),
-// GR lanes each (GR = REPAIR_BLOCK: a block per eigenvalue; GR = 64: a
-// wavefront per eigenvalue, REPAIR_BLOCK/64 of them sharing the block's staged
-// arrays): the repairs are a handful of eigenvalues with several O(n) passes
-// apiece, so they get their own launch instead of stretching k_check.
-// Groups beyond the list length skip the work.  When the arrowhead was
-// deflated, the last block to finish then places the deflated eigenpairs
-// among the solved ones, whose values are all final at that point.
-constexpr int REPAIR_BLOCK = 256;
+struct FinStage {
+  double pv[FIN_COLS], sf[FIN_COLS], mu[FIN_COLS], inrm[FIN_COLS], sig[FIN_COLS];
+  int col[FIN_COLS];     // output column, -1: none (past a deflated problem's order, or a redo block's)
+  int redo[BLOCK];       // eigenvalues this block re-solves
+  int redo_count;
+};
 
-template <int KIND, bool STAGE, int GR>
-__global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt) {
-  extern __shared__ double lds[];
-  constexpr int PER = REPAIR_BLOCK / GR;       // repairs per block
-  const Ws w = ws_view(D.ws, D.n);
-  const uint32_t count = min(*repair_count(w), (uint32_t)D.n);
-  if (blockIdx.x * PER < count) {
-    if constexpr (STAGE) stage_hot(D, lds);
-    const uint32_t* list = repair_list(w, D.n);
-    const int grp = threadIdx.x / GR, ln = threadIdx.x % GR;
-    for (uint32_t q = blockIdx.x * PER + grp; q < count; q += gridDim.x * PER) {
-      const int k = (int)list[q];
-      if (k < 0 || k >= D.n) continue;
-      if constexpr (STAGE) check_body<KIND, GR, true>(D, opt, k, ln, lds, lds + sorted_count(D));
-      else check_body<KIND, GR>(D, opt, k, ln);
+template <int KIND, int W, int RPT>
+__device__ inline void finish_rows(const ProbDesc& D, int rt, int nc, const FinStage& L) {
+  static_assert(W == 1 || W == 2, "one or two rows per store");
+  static_assert(RPT % W == 0, "rows per thread");
+  constexpr int PER = RPT / W;   // stores per column per thread
+  const int n = D.n;
+  const int r0 = rt * BLOCK * RPT + threadIdx.x * W;
+  double dr[RPT], num[RPT], im[KIND == KIND_HERM ? RPT : 1];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      const int r = r0 + q * BLOCK * W + e;
+      const bool body = (KIND == KIND_DPR1) ? (r < n) : (r < n - 1);
+      dr[q * W + e] = body ? in_pole<KIND>(D, r) : 0.0;
+      if constexpr (KIND == KIND_HERM) {
+        num[q] = body ? D.z[2 * r] : 0.0;
+        im[q] = body ? D.z[2 * r + 1] : 0.0;
+      } else {
+        num[q * W + e] = body ? ((KIND == KIND_SVD) ? dr[q * W + e] * D.z[r] : D.z[r]) : 0.0;
+      }
     }
   }
-  if constexpr (KIND == KIND_ARROW) {
-    if (deflated_count(w) > 0) place_deflated_last(D, w, gridDim.x);
+  for (int c = 0; c < nc; ++c) {
+    const int col = L.col[c];
+    if (col < 0) continue;
+    const double pv = L.pv[c], s = L.sf[c], mu = L.mu[c], inrm = L.inrm[c];
+    const double sigma = (KIND == KIND_SVD) ? L.sig[c] : 0.0;
+    double* vc = D.V + (size_t)col * (size_t)D.ldv * (KIND == KIND_HERM ? 2 : 1);
+    double* uc = (KIND == KIND_SVD && D.U) ? D.U + (size_t)col * (size_t)D.ldu : nullptr;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int r = r0 + q * BLOCK * W;
+      if (r >= n) continue;   // W = 2: n is even, so r + 1 < n as well
+      if constexpr (KIND == KIND_HERM) {
+        double ur, ui;
+        vec_entry_c(dr[q], num[q], im[q], r == n - 1, pv, s, mu, inrm, &ur, &ui);
+        const v2d u = {ur, ui};
+        __builtin_nontemporal_store(u, (v2d*)vc + r);
+      } else if constexpr (W == 1) {
+        const double v = vec_entry<KIND>(dr[q], num[q], r == n - 1, pv, s, mu, inrm);
+        __builtin_nontemporal_store(v, vc + r);
+        if (KIND == KIND_SVD && uc) __builtin_nontemporal_store(svd_left(D, sigma, v, r), uc + r);
+      } else {
+        const double v0 = vec_entry<KIND>(dr[2 * q], num[2 * q], false, pv, s, mu, inrm);
+        const double v1 = vec_entry<KIND>(dr[2 * q + 1], num[2 * q + 1], r + 1 == n - 1, pv, s, mu, inrm);
+        const v2d vv = {v0, v1};
+        __builtin_nontemporal_store(vv, (v2d*)(vc + r));
+        if (KIND == KIND_SVD && uc) {
+          const v2d uu = {svd_left(D, sigma, v0, r), svd_left(D, sigma, v1, r + 1)};
+          __builtin_nontemporal_store(uu, (v2d*)(uc + r));
+        }
+      }
+    }
   }
 }
 
-// cols <= VEC_COLS_MAX (vec_shape).  A single problem's tiles read their
-// columns' shift data straight from the workspace: staged in LDS first they
-// were slower at n = 4096 (27.8 against 25.7 us) and equal at n = 16384.
-#ifndef AHD_SINGLE_VEC_STAGE
-#define AHD_SINGLE_VEC_STAGE 0
-#endif
-template <int KIND, int W, int RPT>
-__global__ __launch_bounds__(BLOCK) void k_vec(ProbDesc D, int row_tiles, int cols) {
-  __shared__ VecTileStage L;
-  const int ct = blockIdx.x / row_tiles;
-  vec_tile<KIND, W, RPT, VecTileStage, AHD_SINGLE_VEC_STAGE != 0>(D, blockIdx.x - ct * row_tiles, ct, cols, L);
+// column data of the finished eigenvalue k into slot c (its final shift pair is
+// in the workspace)
+template <int KIND>
+__device__ inline void finish_stage(const ProbDesc& D, const Ws& w, int k, int c, FinStage& L) {
+  int col = k;
+  if constexpr (KIND == KIND_ARROW) {
+    const int nd = deflated_count(w);
+    if (nd > 0) col = (k <= reduced_m(w)) ? k + count_above(w.dv, nd, w.lr[k], false) : -1;
+  }
+  if constexpr (KIND == KIND_DPR1) {
+    if (D.neg) col = D.n - 1 - k;
+  }
+  L.col[c] = col;
+  if (col < 0) return;
+  L.pv[c] = w.pv[col];
+  L.sf[c] = w.sf[col];
+  L.mu[c] = w.mu[col];
+  L.inrm[c] = w.inrm[col];
+  if constexpr (KIND == KIND_SVD) L.sig[c] = D.lam[col];
 }
 
-template <int RPT>
-__global__ __launch_bounds__(BLOCK) void k_vec_c(ProbDesc D, int row_tiles, int cols) {
-  __shared__ VecTileStage L;
-  const int ct = blockIdx.x / row_tiles;
-  vec_tile_c<RPT>(D, blockIdx.x - ct * row_tiles, ct, cols, L);
+template <int KIND, int W, int RPT>
+__global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int redo_blocks, int cols) {
+  extern __shared__ double lds[];
+  constexpr int SK = (KIND == KIND_HERM) ? KIND_ARROW : KIND;   // solved as the real arrowhead on |z|
+  __shared__ FinStage L;
+  const Ws w = ws_view(D.ws, D.n);
+  const int t = threadIdx.x;
+  const bool redo = (int)blockIdx.x < redo_blocks;
+  const int step = redo ? redo_blocks : 1;
+  const int k0 = redo ? (int)blockIdx.x : ((int)blockIdx.x - redo_blocks) * cols;
+  const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);   // at most FIN_MAX / redo_blocks, cols
+  if (t == 0) L.redo_count = 0;
+  __syncthreads();
+  if (t < mine) {
+    const int k = k0 + t * step;
+    const bool ask = check_body<SK, 1, false, DEFER_BLOCK>(D, opt, k, 0, nullptr, nullptr, !redo);
+    if (redo && ask) L.redo[atomicAdd(&L.redo_count, 1)] = k;
+    if (!redo && D.V) {
+      if (ask) L.col[t] = -1;
+      else finish_stage<KIND>(D, w, k, t, L);
+    }
+  }
+  __syncthreads();
+  const int count = redo ? L.redo_count : (D.V ? mine : 0);
+  if (redo && count > 0) stage_hot(D, lds);
+  for (int q0 = 0; q0 < count; q0 += FIN_COLS) {
+    const int nc = min(FIN_COLS, count - q0);
+    if (redo) {
+      for (int q = 0; q < nc; ++q) {
+        check_body<SK, BLOCK, true>(D, opt, L.redo[q0 + q], t, lds, lds + sorted_count(D));
+        if (t == 0 && D.V) finish_stage<KIND>(D, w, L.redo[q0 + q], q, L);   // thread 0 wrote what it reads
+      }
+      if (!D.V) continue;
+      __syncthreads();
+    }
+    for (int rt = 0; rt * BLOCK * RPT < D.n; ++rt) finish_rows<KIND, W, RPT>(D, rt, nc, L);
+    if (redo) __syncthreads();
+  }
+}
+
+// One lane per eigenvalue, in small blocks that spread over the compute units:
+// scalar work bound by latency.  Eigenvalues that need a repair are listed.
+constexpr int CHECK_BLOCK = 64;
+
+template <int KIND>
+__global__ __launch_bounds__(CHECK_BLOCK) void k_check(ProbDesc D, Options opt) {
+  const int k = (int)(blockIdx.x * CHECK_BLOCK + threadIdx.x);
+  if (k >= D.n) return;
+  if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0)) defer_repair(ws_view(D.ws, D.n), D.n, k, 0);
+}
+
+// The listed eigenvalues, a block each; blocks beyond the list's length return.
+constexpr int REPAIR_BLOCK = 256;
+
+template <int KIND, bool STAGE>
+__global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt) {
+  extern __shared__ double lds[];
+  const Ws w = ws_view(D.ws, D.n);
+  const uint32_t count = min(*repair_count(w), (uint32_t)D.n);
+  if (blockIdx.x >= count) return;
+  if constexpr (STAGE) stage_hot(D, lds);
+  const uint32_t* list = repair_list(w, D.n);
+  for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
+    const int k = (int)list[q];
+    if (k < 0 || k >= D.n) continue;
+    check_body<KIND, REPAIR_BLOCK, STAGE>(D, opt, k, threadIdx.x, lds, lds + sorted_count(D));
+  }
+}
+
+// BLOCK * RPT rows of `cols` columns a block
+template <int KIND, int W, int RPT>
+__global__ __launch_bounds__(BLOCK) void k_vec(ProbDesc D, int row_tiles, int cols) {
+  __shared__ FinStage L;
+  const Ws w = ws_view(D.ws, D.n);
+  const int ct = blockIdx.x / row_tiles, k0 = ct * cols;
+  const int nc = min(D.n - k0, cols);
+  if ((int)threadIdx.x < nc) finish_stage<KIND>(D, w, k0 + threadIdx.x, threadIdx.x, L);
+  __syncthreads();
+  finish_rows<KIND, W, RPT>(D, blockIdx.x - ct * row_tiles, nc, L);
+}
+
+// The deflated eigenpairs of a reducible arrowhead: placed among the solved ones,
+// whose values are final after k_finish, and their vectors.  A block each, in
+// turn; for the usual irreducible input every block returns at once.
+__global__ __launch_bounds__(BLOCK) void k_defl(ProbDesc D) {
+  __shared__ int col;
+  const Ws w = ws_view(D.ws, D.n);
+  const int nd = deflated_count(w);
+  for (int s = blockIdx.x; s < nd; s += gridDim.x) {
+    if (threadIdx.x == 0) col = place_deflated(D, w, s);
+    __syncthreads();
+    if (D.V) {
+      double* vc = D.V + (size_t)col * (size_t)D.ldv;
+      for (int r = threadIdx.x; r < D.n; r += BLOCK)
+        __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
+    }
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -284,41 +560,41 @@ static void launch_timed(F kern, dim3 grid, dim3 block, size_t lds, hipStream_t 
   else hipLaunchKernelGGL(kern, grid, block, lds, st, args...);
 }
 
-// the check with one lane per eigenvalue and nothing staged is latency-bound
-// scalar work: small blocks spread it over more compute units
-constexpr int CHECK_LANE_BLOCK = 64;
-
 template <int KIND, int G>
-static void launch_rc(const ProbDesc& D, const Options& opt, hipStream_t st, bool check, size_t lds,
-                      hipEvent_t e0, hipEvent_t e1) {
-  const int64_t threads = (int64_t)D.n * G;
-  if (check && G == 1 && lds == 0) {
-    const dim3 grid((unsigned)((threads + CHECK_LANE_BLOCK - 1) / CHECK_LANE_BLOCK));
-    launch_timed(k_check<KIND, G, false>, grid, dim3(CHECK_LANE_BLOCK), 0, st, e0, e1, D, opt);
-    return;
-  }
-  const dim3 grid((unsigned)((threads + ROOT_BLOCK - 1) / ROOT_BLOCK));
-  if (lds > 0) {
-    if (!check) launch_timed(k_root<KIND, G, true>, grid, dim3(ROOT_BLOCK), lds, st, e0, e1, D, opt);
-    else launch_timed(k_check<KIND, G, true>, grid, dim3(ROOT_BLOCK), lds, st, e0, e1, D, opt);
-  } else {
-    if (!check) launch_timed(k_root<KIND, G, false>, grid, dim3(ROOT_BLOCK), 0, st, e0, e1, D, opt);
-    else launch_timed(k_check<KIND, G, false>, grid, dim3(ROOT_BLOCK), 0, st, e0, e1, D, opt);
-  }
+static void launch_root(const ProbDesc& D, const Options& opt, hipStream_t st, size_t lds, hipEvent_t e0,
+                        hipEvent_t e1) {
+  const dim3 grid((unsigned)(((int64_t)D.n * G + ROOT_BLOCK - 1) / ROOT_BLOCK));
+  if (lds > 0) launch_timed(k_root<KIND, G, true>, grid, dim3(ROOT_BLOCK), lds, st, e0, e1, D, opt);
+  else launch_timed(k_root<KIND, G, false>, grid, dim3(ROOT_BLOCK), 0, st, e0, e1, D, opt);
 }
 
 template <int KIND>
-static void launch_rc_any(int G, const ProbDesc& D, const Options& opt, hipStream_t st, bool check, size_t lds,
-                          hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
+static void launch_root_any(int G, const ProbDesc& D, const Options& opt, hipStream_t st, size_t lds, hipEvent_t e0,
+                            hipEvent_t e1) {
   switch (G) {
-    case 1: launch_rc<KIND, 1>(D, opt, st, check, lds, e0, e1); break;
-    case 2: launch_rc<KIND, 2>(D, opt, st, check, lds, e0, e1); break;
-    case 4: launch_rc<KIND, 4>(D, opt, st, check, lds, e0, e1); break;
-    case 8: launch_rc<KIND, 8>(D, opt, st, check, lds, e0, e1); break;
-    case 16: launch_rc<KIND, 16>(D, opt, st, check, lds, e0, e1); break;
-    case 32: launch_rc<KIND, 32>(D, opt, st, check, lds, e0, e1); break;
-    default: launch_rc<KIND, 64>(D, opt, st, check, lds, e0, e1); break;
+    case 1: launch_root<KIND, 1>(D, opt, st, lds, e0, e1); break;
+    case 2: launch_root<KIND, 2>(D, opt, st, lds, e0, e1); break;
+    case 4: launch_root<KIND, 4>(D, opt, st, lds, e0, e1); break;
+    case 8: launch_root<KIND, 8>(D, opt, st, lds, e0, e1); break;
+    case 16: launch_root<KIND, 16>(D, opt, st, lds, e0, e1); break;
+    case 32: launch_root<KIND, 32>(D, opt, st, lds, e0, e1); break;
+    default: launch_root<KIND, 64>(D, opt, st, lds, e0, e1); break;
   }
+}
+
+// Rows per thread and columns per block of the vectors: whole columns up to
+// FIN_MAX (k_finish), few of them so that the grid keeps a few hundred blocks;
+// above (k_vec) wide tiles around n = 4096 and tall ones for larger n.
+struct VecShape {
+  int rpt, cols;
+};
+
+static VecShape vec_shape(int64_t n) {
+  if (n > 4096) return VecShape{8, 16};
+  if (n > 2048) return VecShape{4, 32};
+  if (n > FIN_MAX) return VecShape{4, 8};
+  if (n > 512) return VecShape{4, 4};
+  return VecShape{2, n > 256 ? 2 : 1};
 }
 
 template <int KIND>
@@ -346,15 +622,19 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
   // a timed call takes the event set the previous timed call did not use
   const int es = (tm && h->timed_calls > 0) ? 1 - h->ev_set : 0;
   hipEvent_t* ev = h->ev[es];
-  auto mark = [&](int e) {
-    if (tm) (void)hipEventRecord(ev[e], st);
-  };
   auto at = [&](int e) -> hipEvent_t { return tm ? ev[e] : nullptr; };
   const int ms = sorted_count(D);
   // every stage boundary is the start (or end) of a kernel
-  launch_timed(k_front<KIND>, dim3(1), dim3(FRONT_BLOCK), 0, st, at(0), nullptr, D);
-  if (ms == 0) mark(1);
-  if (ms > 0) {
+  if (ms <= PREP_MAX) {
+    if (ms <= PREP_ONE) {
+      const int groups = ms <= 64 ? 1 : (ms <= 128 ? 2 : 4);
+      launch_timed(k_prep<KIND, true>, dim3(1), dim3(PREP_BLOCK), 0, st, at(0), at(1), D, D.d, groups);
+    } else {
+      launch_timed(k_prep<KIND, false>, dim3((unsigned)((ms + 63) / 64)), dim3(PREP_BLOCK), 0, st, at(0), at(1), D,
+                   D.d, 1);
+    }
+  } else {
+    launch_timed(k_front<KIND>, dim3(1), dim3(FRONT_BLOCK), 0, st, at(0), nullptr, D);
     // about SORT_GRID blocks in all (they return at once when k_front found the
     // order), each comparing its key tile against one or more chunks
     constexpr int64_t SORT_GRID = 256;
@@ -364,55 +644,56 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
     launch_timed(k_sort<KIND>, dim3((unsigned)jt, (unsigned)lc), dim3(SORT_BLOCK), 0, st, at(1), nullptr, D,
                  SORT_CHUNK, (int)nchunks);
   }
-  // the root and vector stages are timed by their kernels' own start and end;
+  // the root and finish stages are timed by their kernels' own start and end;
   // the stages between take up the dispatch gaps
   const int G = single_lanes(h, D.n);
   const size_t hot = (size_t)(ms + D.n - 1) * sizeof(double);
   const size_t lds = (hot <= h->lds_max) ? hot : 0;
-  launch_rc_any<SK>(G, D, h->opt, st, false, lds, at(2), at(3));
-  // the check stage reads the poles only for DPR1 norms or after bisection;
-  // otherwise the root pass left the norm and what remains per eigenvalue is
-  // scalar work: one lane each, no staged copy
-  const bool check_reads_poles = SK == KIND_DPR1 || h->opt.root != ROOT_RATIONAL;
-  if (check_reads_poles) launch_rc_any<SK>(G, D, h->opt, st, true, lds);
-  else launch_rc_any<SK>(1, D, h->opt, st, true, 0);
+  launch_root_any<SK>(G, D, h->opt, st, lds, at(2), at(3));
   {
-    // deferred repairs; the block reductions add a little static LDS
-    const size_t lds_r = (hot + 4096 <= h->lds_max) ? hot : 0;
-    constexpr int GR = REPAIR_BLOCK;   // a block per repair (measured faster than a wavefront for n >= 4096)
-    const dim3 grid((unsigned)std::min<int64_t>((D.n + REPAIR_BLOCK / GR - 1) / (REPAIR_BLOCK / GR), h->cus));
-    if (lds_r > 0) hipLaunchKernelGGL((k_repair<SK, true, GR>), grid, dim3(REPAIR_BLOCK), lds_r, st, D, h->opt);
-    else hipLaunchKernelGGL((k_repair<SK, false, GR>), grid, dim3(REPAIR_BLOCK), 0, st, D, h->opt);
-  }
-  hipEvent_t v0 = D.V ? at(4) : nullptr, v1 = D.V ? at(5) : nullptr;
-  if (!v0) mark(4);
-  if (KIND == KIND_HERM && D.V) {
     const VecShape sh = vec_shape(D.n);
-    const int row_tiles = (int)((D.n + (int64_t)BLOCK * sh.rpt - 1) / ((int64_t)BLOCK * sh.rpt));
-    const int col_chunks = (D.n + sh.cols - 1) / sh.cols;
-    const dim3 grid((unsigned)((int64_t)row_tiles * col_chunks));
-    if (sh.rpt == 8) launch_timed(k_vec_c<8>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-    else if (sh.rpt == 2) launch_timed(k_vec_c<2>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-    else launch_timed(k_vec_c<4>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-  } else if (D.V) {
-    const VecShape sh = vec_shape(D.n);
-    const int row_tiles = (int)((D.n + (int64_t)BLOCK * sh.rpt - 1) / ((int64_t)BLOCK * sh.rpt));
-    const int col_chunks = (D.n + sh.cols - 1) / sh.cols;
-    const dim3 grid((unsigned)((int64_t)row_tiles * col_chunks));
-    const bool pair = (D.n % 2 == 0) && (D.ldv % 2 == 0) && (((uintptr_t)D.V & 15) == 0) &&
+    // 16-byte stores: a complex entry each, or two rows where every column starts on 16 bytes
+    const bool pair = KIND != KIND_HERM && (D.n % 2 == 0) && (D.ldv % 2 == 0) && (((uintptr_t)D.V & 15) == 0) &&
                       (!D.U || ((D.ldu % 2 == 0) && (((uintptr_t)D.U & 15) == 0)));
-    if (sh.rpt == 8) {
-      if (pair) launch_timed(k_vec<KIND, 2, 8>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-      else launch_timed(k_vec<KIND, 1, 8>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-    } else if (sh.rpt == 2) {
-      if (pair) launch_timed(k_vec<KIND, 2, 2>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-      else launch_timed(k_vec<KIND, 1, 2>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
+    constexpr int W2 = KIND == KIND_HERM ? 1 : 2;
+    auto by_shape = [&](auto&& go) {   // go(rows per store, rows per thread)
+      using one = std::integral_constant<int, 1>;
+      using two = std::integral_constant<int, W2>;
+      if (sh.rpt == 8) { if (pair) go(two(), std::integral_constant<int, 8>()); else go(one(), std::integral_constant<int, 8>()); }
+      else if (sh.rpt == 4) { if (pair) go(two(), std::integral_constant<int, 4>()); else go(one(), std::integral_constant<int, 4>()); }
+      else { if (pair) go(two(), std::integral_constant<int, 2>()); else go(one(), std::integral_constant<int, 2>()); }
+    };
+    if (D.n <= FIN_MAX) {
+      const int redo_blocks = (int)std::min<int64_t>(D.n, h->cus);
+      const int cols = D.V ? sh.cols : FIN_VALUES;
+      const dim3 grid((unsigned)(redo_blocks + (D.n + cols - 1) / cols));
+      by_shape([&](auto wd, auto rpt) {
+        if constexpr (decltype(rpt)::value <= 4)
+          launch_timed(k_finish<KIND, decltype(wd)::value, decltype(rpt)::value>, grid, dim3(BLOCK), hot, st, at(4),
+                       at(5), D, h->opt, redo_blocks, cols);
+      });
     } else {
-      if (pair) launch_timed(k_vec<KIND, 2, 4>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
-      else launch_timed(k_vec<KIND, 1, 4>, grid, dim3(BLOCK), 0, st, v0, v1, D, row_tiles, sh.cols);
+      hipLaunchKernelGGL(k_check<SK>, dim3((unsigned)((D.n + CHECK_BLOCK - 1) / CHECK_BLOCK)), dim3(CHECK_BLOCK), 0, st,
+                         D, h->opt);
+      const size_t lds_r = (hot + 4096 <= h->lds_max) ? hot : 0;   // the block reductions add a little static LDS
+      const dim3 grid((unsigned)std::min<int64_t>(D.n, h->cus));
+      hipEvent_t r0 = D.V ? nullptr : at(4), r1 = D.V ? nullptr : at(5);
+      if (lds_r > 0) launch_timed(k_repair<SK, true>, grid, dim3(REPAIR_BLOCK), lds_r, st, r0, r1, D, h->opt);
+      else launch_timed(k_repair<SK, false>, grid, dim3(REPAIR_BLOCK), 0, st, r0, r1, D, h->opt);
+      if (D.V) {
+        by_shape([&](auto wd, auto rpt) {
+          if constexpr (decltype(rpt)::value >= 4) {
+            const int row_tiles = (int)((D.n + (int64_t)BLOCK * sh.rpt - 1) / ((int64_t)BLOCK * sh.rpt));
+            const int64_t chunks = (D.n + sh.cols - 1) / sh.cols;
+            launch_timed(k_vec<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(row_tiles * chunks)),
+                         dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, sh.cols);
+          }
+        });
+      }
     }
   }
-  if (!v1) mark(5);
+  if (KIND == KIND_ARROW && D.n > 1)
+    hipLaunchKernelGGL(k_defl, dim3((unsigned)std::min<int64_t>(D.n - 1, h->cus)), dim3(BLOCK), 0, st, D);
   if (tm) {
     h->ev_set = es;
     h->timed_calls = std::min(h->timed_calls + 1, 2);

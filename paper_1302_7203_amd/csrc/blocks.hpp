@@ -188,7 +188,6 @@ __device__ inline void sort_block(const ProbDesc& D) {
 // writes one entry per row and column.  W = 2 lets a lane write two
 // consecutive rows with one 16-byte non-temporal store (n and the leading
 // dimensions even, V and U 16-byte aligned); W = 1 writes one row per store.
-// The measured best tile shape depends on n (vec_shape).
 //
 // The block's column data (shift pole, offset, mu, 1/||x||, ...) is staged in
 // LDS before the column loop: read from the workspace inside the loop, each
@@ -203,7 +202,6 @@ constexpr int VEC_TILE = BLOCK * VEC_RPT;      // rows per block
 #define AHD_VEC_COLS 8
 #endif
 constexpr int VEC_COLS = AHD_VEC_COLS;         // columns per block (batched path)
-constexpr int VEC_COLS_MAX = 32;               // most columns a row-tile block takes (vec_shape)
 constexpr int VEC_FLAT_COLS = 256;             // most columns a flat tile takes
 #ifndef AHD_VEC_FLAT_ROWS
 #define AHD_VEC_FLAT_ROWS 512
@@ -218,23 +216,7 @@ struct VecStage {
   int cm[C];
   double dr[R], num[R];
 };
-using VecTileStage = VecStage<VEC_COLS_MAX, 1>;
 using VecFlatStage = VecStage<VEC_FLAT_COLS, VEC_FLAT_ROWS>;
-
-struct VecShape {
-  int rpt, cols;
-};
-
-// rows per thread and columns per block for a single problem of order n:
-// tall tiles for large n, wide ones around n = 4096, and for smaller n narrow
-// ones so that the grid keeps a few hundred blocks
-__host__ __device__ inline VecShape vec_shape(int64_t n) {
-  if (n > 4096) return VecShape{8, 16};
-  if (n > 2048) return VecShape{4, 32};
-  if (n > 1024) return VecShape{4, 8};
-  if (n > 512) return VecShape{4, 4};
-  return VecShape{2, n >= 512 ? 2 : 1};
-}
 
 // columns [c0, c0 + nc) of the workspace's final shift pairs into L (every
 // thread of the block calls this; it ends with a barrier)
@@ -252,7 +234,7 @@ __device__ inline void stage_cols(const ProbDesc& D, const Ws& w, int c0, int nc
   __syncthreads();
 }
 
-template <int KIND, int W, int RPT, class S, bool STAGE = true>
+template <int KIND, int W, int RPT, class S>
 __device__ inline void vec_tile(const ProbDesc& D, int rt, int ct, int cols, S& L) {
   static_assert(W == 1 || W == 2, "one or two rows per store");
   static_assert(RPT % W == 0, "rows per thread");
@@ -274,12 +256,12 @@ __device__ inline void vec_tile(const ProbDesc& D, int rt, int ct, int cols, S& 
   const int c0 = ct * cols;
   const int nc = min(n - c0, cols);
   const int nd = (KIND == KIND_ARROW) ? deflated_count(w) : 0;
-  if constexpr (STAGE) stage_cols<KIND>(D, w, c0, nc, nd, L);
+  stage_cols<KIND>(D, w, c0, nc, nd, L);
   for (int c = 0; c < nc; ++c) {
     const int col = c0 + c;
     double* vc = D.V + (size_t)col * (size_t)D.ldv;
     if (KIND == KIND_ARROW && nd > 0) {
-      const int it = STAGE ? L.cm[c] : w.cm[col];
+      const int it = L.cm[c];
       if (it >= 0 && it < nd) {   // a deflated eigenvector (the whole block takes this branch)
         auto entry = [&](int r, double zr) { return r < n - 1 ? deflated_entry(w, it, w.iperm[r], zr) : 0.0; };
 #pragma unroll
@@ -297,10 +279,9 @@ __device__ inline void vec_tile(const ProbDesc& D, int rt, int ct, int cols, S& 
         continue;
       }
     }
-    const double pv = STAGE ? L.pv[c] : w.pv[col], s = STAGE ? L.sf[c] : w.sf[col];
-    const double mu = STAGE ? L.mu[c] : w.mu[col], inrm = STAGE ? L.inrm[c] : w.inrm[col];
+    const double pv = L.pv[c], s = L.sf[c], mu = L.mu[c], inrm = L.inrm[c];
     double* uc = (KIND == KIND_SVD && D.U) ? D.U + (size_t)col * (size_t)D.ldu : nullptr;
-    const double sigma = (KIND == KIND_SVD) ? (STAGE ? L.sig[c] : D.lam[col]) : 0.0;
+    const double sigma = (KIND == KIND_SVD) ? L.sig[c] : 0.0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int r = rt * TILE + q * BLOCK * W + threadIdx.x * W;

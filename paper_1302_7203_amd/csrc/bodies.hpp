@@ -180,20 +180,18 @@ __host__ __device__ inline double sort_key(double d) {
 
 // status of input j: reducibility (Sec. 1) and domain checks
 template <int KIND>
-__host__ __device__ inline uint32_t input_status(const ProbDesc& D, int j, bool dup) {
+__host__ __device__ inline uint32_t input_status_vals(double dj, double re, double im, bool dup) {
   uint32_t st = 0;
-  const double dj = D.d[j];
-  if constexpr (KIND == KIND_HERM) {
-    const double re = D.z[2 * j], im = D.z[2 * j + 1];
-    if (!finite_d(dj) || !finite_d(re) || !finite_d(im)) st |= INFO_NONFINITE;
-    if ((re == 0.0 && im == 0.0) || dup) st |= INFO_REDUCIBLE;
-  } else {
-    const double zj = D.z[j];
-    if (!finite_d(dj) || !finite_d(zj)) st |= INFO_NONFINITE;
-    if (zj == 0.0 || dup) st |= INFO_REDUCIBLE;
-  }
+  if (!finite_d(dj) || !finite_d(re) || (KIND == KIND_HERM && !finite_d(im))) st |= INFO_NONFINITE;
+  if ((re == 0.0 && (KIND != KIND_HERM || im == 0.0)) || dup) st |= INFO_REDUCIBLE;
   if (KIND == KIND_SVD && dj == 0.0) st |= INFO_BAD_INPUT;
   return st;
+}
+
+template <int KIND>
+__host__ __device__ inline uint32_t input_status(const ProbDesc& D, int j, bool dup) {
+  constexpr int S = (KIND == KIND_HERM) ? 2 : 1;
+  return input_status_vals<KIND>(D.d[j], D.z[S * j], KIND == KIND_HERM ? D.z[S * j + 1] : 0.0, dup);
 }
 
 // sorted entry r from the caller's entry q: the pole, the shaft entry (HERM:
@@ -204,24 +202,30 @@ struct SortedEntry {
   dd c;          // HERM: the weight |z_q|^2 as stored; else unused
 };
 
+// from the values: pole d, shaft entry re (HERM: re + i im)
 template <int KIND>
-__host__ __device__ inline SortedEntry put_sorted_v(const ProbDesc& D, const Ws& w, int r, int q) {
+__host__ __device__ inline SortedEntry put_sorted_vals(const Ws& w, int r, int q, double d, double re, double im) {
   SortedEntry e;
-  e.d = in_pole<KIND>(D, q);
+  e.d = d;
   e.c = dd_from(0.0);
   w.ds[r] = e.d;
   if constexpr (KIND == KIND_HERM) {
-    const double re = D.z[2 * q], im = D.z[2 * q + 1];
     e.c = dd_add(two_prod(re, re), two_prod(im, im));
     w.ch[r] = e.c.hi;
     w.cl[r] = e.c.lo;
     e.z = hypot(re, im);   // |z_q| rounded (only the bounds use it); exact when im = 0
   } else {
-    e.z = D.z[q];
+    e.z = re;
   }
   w.zs[r] = e.z;
   if constexpr (KIND == KIND_ARROW) w.iperm[q] = r;
   return e;
+}
+
+template <int KIND>
+__host__ __device__ inline SortedEntry put_sorted_v(const ProbDesc& D, const Ws& w, int r, int q) {
+  constexpr int S = (KIND == KIND_HERM) ? 2 : 1;
+  return put_sorted_vals<KIND>(w, r, q, in_pole<KIND>(D, q), D.z[S * q], KIND == KIND_HERM ? D.z[S * q + 1] : 0.0);
 }
 
 template <int KIND>
@@ -369,8 +373,8 @@ __host__ __device__ inline double deflated_entry(const Ws& w, int s, int j, doub
 // Output columns are the merge of the reduced eigenvalues (descending, as
 // computed) with the deflated ones (descending); on a tie the reduced one
 // comes first.  Reduced eigenvalue k goes to column k + #{deflated > lambda_k},
-// deflated item s to column s + #{reduced >= delta_s}.
-__host__ __device__ inline void place_deflated(const ProbDesc& D, const Ws& w, int s) {
+// deflated item s to column s + #{reduced >= delta_s} (which place_deflated returns).
+__host__ __device__ inline int place_deflated(const ProbDesc& D, const Ws& w, int s) {
   const int np = reduced_m(w) + 1;
   const double v = w.dv[s];
   const int col = s + count_above(w.lr, np, v, true);
@@ -381,6 +385,7 @@ __host__ __device__ inline void place_deflated(const ProbDesc& D, const Ws& w, i
   w.pv[col] = v; w.sf[col] = 0.0; w.mu[col] = 0.0; w.inrm[col] = 0.0;
   w.kbc[col] = NAN; w.knu[col] = NAN;
   w.cm[col] = s;
+  return col;
 }
 
 // ---------------------------------------------------------------------------
@@ -533,17 +538,18 @@ __host__ __device__ inline void root_body(const ProbDesc& D, const Options& opt,
 // K_nu test and remedies (Algorithm 5, last part; Remarks 1 and 2), then the
 // eigenvector norm.  Writes the final shift pair and the caller's outputs.
 //
-// DEFER = DEFER_ALL: an eigenvalue that needs one of the O(n)-per-step repairs
-// (Remark 1, Remark 2, the DPR1 re-measure from d_n) is only appended to the
-// problem's repair list and left for a second launch, which runs check_body on
-// the listed eigenvalues with a whole block each; everything else is finished
-// here.  DEFER = DEFER_NEAR_ZERO: only Remark 1 is listed (its exact sum of f(0)
-// runs on whole wavefronts); Remark 2 and the DPR1 re-measure run here on the
-// caller's G lanes, as the first pass does.  DEFER = DEFER_WAVE: Remark 1 is
-// listed as for DEFER_NEAR_ZERO; an eigenvalue that needs Remark 2 or the DPR1
-// re-measure writes nothing and makes the call return true, and the caller runs
-// check_body on it again (DEFER_NEAR_ZERO) with all lanes of its wavefront.
-// Every other call returns false.
+// DEFER = DEFER_BLOCK: an eigenvalue that needs an O(n) pass -- a repair (Remark
+// 1, Remark 2, the DPR1 re-measure from d_n) or a norm the root pass did not
+// leave -- writes nothing and makes the call return true, and the caller runs
+// check_body on it again (DEFER_NONE) with a whole block; everything else is
+// finished here, one lane each (commit = false: the same answer, and nothing is
+// written).  DEFER = DEFER_NEAR_ZERO: only Remark 1 is
+// listed (its exact sum of f(0) runs on whole blocks); Remark 2 and the DPR1
+// re-measure run here on the caller's G lanes, as the first pass does.  DEFER =
+// DEFER_WAVE: Remark 1 is listed as for DEFER_NEAR_ZERO; an eigenvalue that needs
+// Remark 2 or the DPR1 re-measure writes nothing and makes the call return true,
+// and the caller runs check_body on it again (DEFER_NEAR_ZERO) with all lanes of
+// its wavefront.  Every other call returns false.
 // The list reuses the sort's rank array, free once the poles are sorted; its
 // length sits in hdr[6] and is cleared by the prologue.
 
@@ -604,20 +610,22 @@ __host__ __device__ inline void defer_repair(const Ws& w, int64_t n, int k, int 
   repair_list(w, n)[at] = (uint32_t)k;
 }
 
-constexpr int DEFER_NONE = 0, DEFER_ALL = 1, DEFER_NEAR_ZERO = 2, DEFER_WAVE = 3;
+constexpr int DEFER_NONE = 0, DEFER_BLOCK = 1, DEFER_NEAR_ZERO = 2, DEFER_WAVE = 3;
 
 template <int KIND, int G, bool HOT = false, int DEFER = DEFER_NONE>
 __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt, int k, int ln,
-                                           const double* hot_d = nullptr, const double* hot_c = nullptr) {
+                                           const double* hot_d = nullptr, const double* hot_c = nullptr,
+                                           bool commit = true) {
   const Ws w = ws_view(D.ws, D.n);
   const Prob P = make_prob<HOT>(D, w, hot_d, hot_c);
   const uint32_t pf = *prob_flags(w);
+  constexpr bool ASK = DEFER == DEFER_BLOCK;
   if (k >= P.n) {
-    if (ln == 0) { w.cnt[6 * k + 3] = 0; w.cnt[6 * k + 4] = 0; w.cnt[6 * k + 5] = 0; }
+    if (ln == 0 && commit) { w.cnt[6 * k + 3] = 0; w.cnt[6 * k + 4] = 0; w.cnt[6 * k + 5] = 0; }
     return false;
   }
   if (pf & INFO_NOT_SOLVED) {
-    if (ln == 0) {
+    if (ln == 0 && commit) {
       w.pv[k] = NAN; w.sf[k] = NAN; w.mu[k] = NAN; w.inrm[k] = NAN;
       w.kbc[k] = NAN; w.knu[k] = NAN;
       D.lam[k] = NAN;
@@ -649,11 +657,8 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
     knu_out = knu;
     const bool zero_pole = w.hdr[2] != 0.0;
     const bool near_zero = quot > opt.tau_zero && !zero_pole;
-    if constexpr (DEFER == DEFER_ALL) {
-      if (near_zero || knu > opt.tau_nu) {
-        defer_repair(w, D.n, k, ln);
-        return false;
-      }
+    if constexpr (ASK) {
+      if (near_zero || knu > opt.tau_nu) return true;
     }
     if constexpr (DEFER == DEFER_NEAR_ZERO || DEFER == DEFER_WAVE) {
       if (near_zero) {
@@ -664,7 +669,7 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
     if constexpr (DEFER == DEFER_WAVE) {
       if (knu > opt.tau_nu) return true;
     }
-    if constexpr (DEFER != DEFER_ALL) {   // the fully deferring check stage returned above
+    if constexpr (!ASK) {   // which returned above
       // Remark 1 runs only where nothing was deferred: its exact sum needs whole wavefronts
       bool r1 = false;
       if constexpr (DEFER == DEFER_NONE) r1 = near_zero;
@@ -744,11 +749,7 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
       const double gap = P.ds[P.nsorted - 2] - dn;
       const double tau = (pv - dn) + s + mu;
       if (tau < 0.5 * gap) {
-        if constexpr (DEFER == DEFER_ALL) {
-          defer_repair(w, D.n, k, ln);
-          return false;
-        }
-        if constexpr (DEFER == DEFER_WAVE) return true;
+        if constexpr (ASK || DEFER == DEFER_WAVE) return true;
         int it = 0;
         const double t2 = dpr1_from_last_pole<G>(P, tau, ln, &it);
         pv = dn; s = 0.0; mu = t2;
@@ -761,6 +762,10 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
   // the first pass's norm holds while its shift and mu stand (no remedy)
   const double nr1 = w.nr1[k];
   const bool first = pv == w.pv1[k] && s == 0.0 && mu == w.mu1[k] && nr1 == nr1;
+  if constexpr (ASK) {
+    if (!first) return true;
+    if (!commit) return false;
+  }
   const double inrm = first ? nr1 : (rn == rn ? rn : inv_norm<KIND, G>(P, pv, s, mu, ln, off_hint));
   if (first || rn == rn) c_plain -= 1;   // no norm pass
   if (ln == 0) {

@@ -61,9 +61,8 @@ __host__ __device__ inline void xacc_add(unsigned long long* acc, double q) {
 #endif
 }
 
-// The accumulated value, rounded (relative error below 2^-52).
-__host__ __device__ inline double xacc_value(const unsigned long long* acc) {
-  uint32_t lim[XL];
+// The accumulated value, rounded (relative error below 2^-52); lim: XL words.
+__host__ __device__ inline double xacc_value(const unsigned long long* acc, uint32_t* lim) {
   long long carry = 0;
   for (int L = 0; L < XL; ++L) {
     const long long v = (long long)acc[L] + carry;
@@ -176,13 +175,15 @@ __host__ __device__ inline double origin_exact(int ln, int nrows, double K, doub
     tail = block_sum_max(tail, false);
     const double badsum = block_sum_max((double)bad, false);
     __shared__ double res;
-    if (threadIdx.x == 0) res = xacc_value(acc);
+    __shared__ uint32_t lim[XL];   // indexed by data: registers would go to scratch memory
+    if (threadIdx.x == 0) res = xacc_value(acc, lim);
     __syncthreads();
     val = res;
     __syncthreads();
     if (badsum > 0.0) return NAN;
 #else
-    val = xacc_value(acc);
+    uint32_t lim[XL];
+    val = xacc_value(acc, lim);
     if (bad) return NAN;
 #endif
     tail *= 1.0 + 0x1p-30;

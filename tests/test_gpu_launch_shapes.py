@@ -1,0 +1,102 @@
+"""Single solves at the orders where their launches change: one block ranks up to 256
+poles alone, several above, the order check's own path above 16384; one launch finishes
+up to n = 1280, three above.  Bars: the oracle at 1e-13 on sampled eigenpairs, and bitwise
+the same result however the poles are ordered."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1302_7203_amd import workloads as W
+from parity import assert_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _solve(pr, **kw):
+    import torch
+    from paper_1302_7203_amd import binding
+    dev = torch.device("cuda", 0)
+    d, z = torch.from_numpy(pr.d.copy()).to(dev), torch.from_numpy(pr.z.copy()).to(dev)
+    f = {W.KIND_ARROW: binding.arrow_eig, W.KIND_DPR1: binding.dpr1_eig, W.KIND_SVD: binding.arrow_svd,
+         W.KIND_HERM: binding.arrow_eig_herm}[pr.kind]
+    out = f(d, z, pr.scalar, **kw)
+    torch.cuda.synchronize(dev)
+    return out
+
+
+def _sampled(pr, out, vectors=True, count=8):
+    ks = np.unique(np.linspace(0, pr.n - 1, min(pr.n, count)).astype(np.int64))
+    if pr.kind == W.KIND_SVD:
+        r = oracle.arrow_svd(pr.d, pr.z, pr.scalar, ks=ks)
+        rl, rV = r.sigma, r.V
+    else:
+        f = {W.KIND_ARROW: oracle.arrow_eig, W.KIND_DPR1: oracle.dpr1_eig, W.KIND_HERM: oracle.herm_eig}[pr.kind]
+        r = f(pr.d, pr.z, pr.scalar, ks=ks)
+        rl, rV = r.lam, r.vec
+    assert_close(out.lam.cpu().numpy()[ks], rl, f"kind {pr.kind} n={pr.n} values")
+    if vectors:
+        V = out.V[:, ks.tolist()].cpu().numpy()
+        if pr.kind == W.KIND_HERM:
+            assert np.max(np.abs(V - rV) / np.abs(rV)) <= 1e-13
+        else:
+            assert_close(V, rV, f"kind {pr.kind} n={pr.n} vectors")
+
+
+def _make(kind, n, rng):
+    return {W.KIND_ARROW: W.uniform_arrow, W.KIND_DPR1: W.dpr1, W.KIND_SVD: W.svd_arrow, W.KIND_HERM: W.herm_arrow}[
+        kind](n, rng)
+
+
+@pytest.mark.parametrize("n", [2, 64, 65, 66, 129, 256, 257, 258, 1280, 1281])
+@pytest.mark.parametrize("kind", [W.KIND_ARROW, W.KIND_DPR1, W.KIND_SVD, W.KIND_HERM])
+def test_orders_at_the_edges_of_the_launches(kind, n, oracle_lib):
+    import torch
+    rng = np.random.default_rng(1000 * kind + n)
+    pr = _make(kind, n, rng)
+    perm = np.argsort(-np.abs(pr.d) if kind == W.KIND_SVD else -pr.d, kind="stable")
+    srt = W.Problem(kind, n, pr.d[perm], pr.z[perm], pr.scalar)
+    base = _solve(srt)
+    _sampled(srt, base)
+    m = pr.d.size
+    for q in (np.arange(m)[::-1].copy(), rng.permutation(m)):
+        out = _solve(W.Problem(kind, n, srt.d[q], srt.z[q], srt.scalar))
+        assert torch.equal(out.lam, base.lam) and torch.equal(out.info, base.info)
+        rows = torch.from_numpy(np.concatenate([q, np.arange(m, n)])).to(base.V.device)
+        assert torch.equal(out.V, base.V[rows])
+
+
+@pytest.mark.parametrize("m", [16384, 16385])
+def test_largest_single_launch_order(m, oracle_lib):
+    import torch
+    rng = np.random.default_rng(m)
+    pr = W.uniform_arrow(m + 1, rng, -1e4, 1e4)
+    base = _solve(pr, vectors=False)
+    _sampled(pr, base, vectors=False, count=4)
+    q = rng.permutation(m)
+    out = _solve(W.Problem(pr.kind, pr.n, pr.d[q], pr.z[q], pr.scalar), vectors=False)
+    assert torch.equal(out.lam, base.lam)
+
+
+@pytest.mark.parametrize("n", [40, 300, 1300])
+def test_equal_poles_and_bad_input_are_seen_in_any_order(n, oracle_lib):
+    """Equal poles of a DPR1 problem and poles that are not numbers are reported, and a
+    reducible arrowhead is deflated, by the block that ranks alone and by several."""
+    rng = np.random.default_rng(n)
+    pr = W.dpr1(n, rng)
+    pr.d[n // 2] = pr.d[3]
+    for q in (np.argsort(-pr.d, kind="stable"), rng.permutation(n)):
+        out = _solve(W.Problem(pr.kind, n, pr.d[q], pr.z[q], pr.scalar))
+        assert bool((out.info.cpu() == 16).all()) and bool(out.lam.isnan().all()) and bool(out.V.isnan().all())
+    bad = W.uniform_arrow(n, rng)
+    bad.d[5] = np.nan
+    out = _solve(bad)
+    assert bool((out.info.cpu() == 32).all()) and bool(out.lam.isnan().all())
+    bad.d[7] = bad.d[2]          # an equal pair beside it
+    assert bool((_solve(bad).info.cpu() == 48).all())
+    red = W.reducible_arrow(n, rng, zero_frac=0.3, repeat_every=4)
+    out = _solve(red)
+    ref = oracle.arrow_eig(red.d, red.z, red.scalar, ks=np.arange(0, n, max(1, n // 40)))
+    ks = np.arange(0, n, max(1, n // 40))
+    assert_close(out.lam.cpu().numpy()[ks], ref.lam, "reducible values")
+    assert_close(out.V.cpu().numpy()[:, ks], ref.vec, "reducible vectors")
+    assert np.array_equal((out.info.cpu().numpy()[ks] & 1024) != 0, ref.tau == 0)
