@@ -80,10 +80,10 @@ typedef struct arrow_handle_s* arrow_handle_t;
                                   runs only above it.  0 = always double-double (default).  With a
                                   bound of a few, eigenvalues carry about K_b times the FP64 sums'
                                   rounding instead of double-double's: a few ulps to ~1e-14 */
-#define ARROW_OPT_CHECK_LANES 9 /* batched plans: lanes per eigenvalue in the check stage (K_nu test,
-                                  norms): 4 (default), 8, 16, 32 or 64, or 0 for those of the first
-                                  pass; the Remark 2 remedies and the DPR1 re-measure that the test
-                                  calls for are re-run on whole wavefronts */
+#define ARROW_OPT_CHECK_LANES 9 /* 0, 4 (default), 8, 16, 32 or 64: accepted for programs that set it.  The batched
+                                  plans' K_nu test takes one lane per eigenvalue and what it lists a
+                                  wavefront each, whatever the value; results never depended on it
+                                  beyond rounding */
 
 /* Create a handle on HIP device `device`.  *h receives the handle. */
 int arrow_create(arrow_handle_t* h, int device);
@@ -248,7 +248,7 @@ typedef struct arrow_batch_s* arrow_batch_t;
 
 #define ARROW_BATCH_GRAPH 1   /* capture the plan's launches in a HIP graph on its first run */
 #define ARROW_BATCH_TIMING 2  /* (without ARROW_BATCH_GRAPH) every run stamps HIP events at the start and end
-                                 of each of its five kernels, by the kernels' own dispatches */
+                                 of each of its five stages, by the kernels' own dispatches */
 
 /* Device bytes a plan for these problems needs (descriptor tables + per-problem workspace). */
 size_t arrow_batch_workspace_size(int64_t count, const arrow_desc_t* descs);
@@ -279,9 +279,9 @@ int arrow_batch_destroy(arrow_batch_t plan);
  * Diagnostics of a plan.
  *
  * arrow_batch_timing: ms[0..4] receive the durations (milliseconds) of the five
- *   kernels of the plan's latest run -- prologue (sort, weights, corner), root
+ *   stages of the plan's latest run, a kernel each but the check stage -- prologue (sort, weights, corner), root
  *   stage (shift, b, root of the inverse, for every eigenvalue), check stage
- *   (K_nu, norms, the repair list), repairs, vectors -- from the events their
+ *   (K_nu, norms, Remark 2; two kernels), repairs (Remark 1), vectors -- from the events their
  *   dispatches stamped (ARROW_BATCH_TIMING).  Waits for that run.
  *   ARROW_ERR_STATE when the plan has no timed run.
  * arrow_batch_counters: out[0..5] receive, summed over all problems p, m_p times

@@ -1,5 +1,5 @@
 // Batched solves: many independent ARROW / DPR1 / SVD / Hermitian problems of
-// uneven order in one plan of five launches.
+// uneven order in one plan of six launches.
 //
 //   k_b_prep    one block per problem: sort (Sec. 1 ordering) and prologue
 //   k_b_root    persistent: every wavefront takes (problem, eigenvalue-group)
@@ -8,10 +8,10 @@
 //               (and weights) from its own LDS slice where they fit, and
 //               regrouping unfinished roots onto wider lane groups; problems
 //               are queued by decreasing order n so the long items start first
-//   k_b_check   a second queue of the same kind for the K_nu test and the
-//               norms; the eigenvalues that need a remedy of Remark 2 or the
-//               DPR1 re-measure are gathered per wavefront and re-solved on
-//               all its lanes; eigenvalues near the origin (Remark 1) are listed
+//   k_b_check   the K_nu test and the outputs, one lane per eigenvalue; the few that
+//               need O(n) passes (Remark 2, the DPR1 re-measure) go to the plan's
+//               list, eigenvalues near the origin (Remark 1) to their problem's
+//   k_b_remedy  the plan's list, a wavefront each
 //   k_b_repair  the listed Remark 1 repairs, a block per eigenvalue; then the
 //               eigenpairs of a deflated arrowhead (Sec. 1) are placed
 //   k_b_vec     every problem's vector tiles (row tiles for large n, flat
@@ -52,13 +52,15 @@ struct BatchArgs {
   const int32_t* lanes;      // G per problem
   const int32_t* vec_start;  // count + 1 prefix sums of vector tiles
   const int32_t* vec_mode;   // per problem: 0 flat tiles, 1 row tiles, 2 row tiles with 16-byte stores
-  const int32_t* check_start;// count + 1 prefix sums of check-stage items
-  const int32_t* check_lanes;// lanes per eigenvalue in the check stage, per problem
+  const int32_t* check_start;// count + 1 prefix sums of check-stage items (WAVE eigenvalues each)
   const int32_t* vec_prob;   // per vector tile: its problem
-  uint32_t* counters;        // [0] first-pass queue, [1] check queue
+  const int32_t* check_prob; // per check-stage item: its problem
+  uint2* redo;               // (problem, eigenvalue) pairs left for k_b_remedy
+  uint32_t* counters;        // [0] first-pass queue, [1] length of redo
   int32_t count;
   int32_t total_items;
   int32_t total_check;
+  int32_t chunk;             // root items taken at a time
 };
 
 __device__ inline int find_problem(const int32_t* start, int count, int x) {
@@ -195,44 +197,15 @@ __device__ __forceinline__ void root_kind(const ProbDesc& D, const Options& opt,
 #endif
 constexpr int ROOT_STAGE = AHD_ROOT_STAGE;
 
-// Check stage of one item: the 64/G eigenvalues k0, k0 + 1, ... of one
-// problem, G lanes each (every lane of the wavefront calls this; lanes past
-// the order idle).  Remark 2 and the DPR1 re-measure -- a few percent of the
-// eigenvalues, each a full re-solve -- are not run on the item's G lanes,
-// which would leave the wavefront's other groups waiting: the eigenvalues that
-// need one are gathered by a ballot and re-run one after the other on all 64
-// lanes.  Only Remark 1 is listed for k_b_repair (its exact sum of f(0) runs on
-// a whole block).
-template <int KIND, int G>
-__device__ inline void check_item(const ProbDesc& D, const Options& opt, int k0, int lane) {
-  const int k = k0 + lane / G, ln = lane & (G - 1);
-  bool need = false;
-  if (k < D.n) need = check_body<KIND, G, false, DEFER_WAVE>(D, opt, k, ln);
-  uint64_t mask = __ballot(need && ln == 0);
-  while (mask) {
-    const int g = __builtin_ctzll(mask) / G;
-    mask &= mask - 1;
-    check_body<KIND, WAVE, false, DEFER_NEAR_ZERO>(D, opt, k0 + g, lane);
-  }
-}
-
-template <int KIND>
-__device__ inline void check_kind(const ProbDesc& D, const Options& opt, int G, int k0, int lane) {
-  switch (G) {
-    case 4: check_item<KIND, 4>(D, opt, k0, lane); break;
-    case 8: check_item<KIND, 8>(D, opt, k0, lane); break;
-    case 16: check_item<KIND, 16>(D, opt, k0, lane); break;
-    case 32: check_item<KIND, 32>(D, opt, k0, lane); break;
-    default: check_item<KIND, 64>(D, opt, k0, lane); break;
-  }
-}
-
-// Items are taken from the queue a chunk at a time (one atomic per chunk): the
-// queue counter is a single L2 address, and with one atomic per item its
-// serialised updates (a few ns each over ~10^6 items) set the stage's time.
-// The check stage's items are short and alike, so its chunks are longer.
+// Root items are taken from the queue a chunk at a time (one atomic per chunk):
+// the queue counter is a single L2 address, and with one atomic per item its
+// serialised updates (a few ns each over ~10^6 items) set the stage's time.  A
+// plan with fewer than CHUNK_FROM items per resident wavefront takes them one by
+// one: an item is 100 us and more of a wavefront's time at n = 2048, and two to a
+// wavefront leave half of the wavefronts idle (32 problems up to n = 2048: 277 us
+// by twos).
 constexpr int ROOT_CHUNK = 2;
-constexpr int CHECK_CHUNK = 8;
+constexpr int CHUNK_FROM = 8;
 
 // at least ROOT_WAVES wavefronts per SIMD: the pole loads come from L2 and need company to hide
 #ifndef AHD_ROOT_WAVES
@@ -247,10 +220,10 @@ __global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(ROO
   int staged = -1;   // the problem whose arrays the slice holds
   for (;;) {
     int first = 0;
-    if (lane == 0) first = (int)atomicAdd(&B.counters[0], (unsigned)ROOT_CHUNK);
-    first = __shfl(first, 0);
+    if (lane == 0) first = (int)atomicAdd(&B.counters[0], (unsigned)B.chunk);
+    first = __builtin_amdgcn_readfirstlane(first);   // the items, their problem and its record are the wavefront's
     if (first >= B.total_items) break;
-    const int last = min(first + ROOT_CHUNK, B.total_items);
+    const int last = min(first + B.chunk, B.total_items);
     for (int item = first; item < last; ++item) {
       const int p = find_problem(B.item_start, B.count, item);
       const ProbDesc D = B.descs[p];
@@ -284,63 +257,129 @@ __global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(ROO
   }
 }
 
-__global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_b_check(BatchArgs B,
-                                                                                                 Options opt) {
+// The K_nu test and the outputs, one lane per eigenvalue: an item is WAVE
+// consecutive eigenvalues of one problem, and the wavefronts stride over the
+// items.  Scalar work bound by latency.  The eigenvalues that need O(n) passes, a
+// few percent, are appended to the plan's list, one atomic a wavefront, and run
+// by k_b_remedy on wavefronts of their own: re-solved in turn by the wavefront
+// that found them, as before, a run of neighbours (a cluster, or a problem of the
+// tridiagonal solver's) held up everything behind it (32 problems up to n = 2048:
+// 107 us, of which the tests are 6).
+constexpr int CHECK_FOUND = 512;   // list entries a block gathers
+
+__global__ __launch_bounds__(STAGE_BLOCK) void k_b_check(BatchArgs B, Options opt) {
   const int lane = threadIdx.x & (WAVE - 1);
-  // the current problem and its items [p_lo, p_hi), kept across items: items
-  // are short, and those of a chunk are consecutive, so the search runs about
-  // once per chunk
-  int p = 0, p_lo = 0, p_hi = 0;
-  for (;;) {
-    int first = 0;
-    if (lane == 0) first = (int)atomicAdd(&B.counters[1], (unsigned)CHECK_CHUNK);
-    first = __builtin_amdgcn_readfirstlane(first);
-    if (first >= B.total_check) break;
-    const int last = min(first + CHECK_CHUNK, B.total_check);
-    for (int item = first; item < last; ++item) {
-      if (item < p_lo || item >= p_hi) {
-        p = find_problem(B.check_start, B.count, item);
-        p_lo = B.check_start[p];
-        p_hi = B.check_start[p + 1];
-      }
-      const ProbDesc D = B.descs[p];
-      const int G = B.check_lanes[p];
-      const int k0 = (item - p_lo) * (WAVE / G);
+  const int step = gridDim.x * (STAGE_BLOCK / WAVE);
+  __shared__ uint2 found[CHECK_FOUND];
+  __shared__ uint32_t nfound, base;
+  if (threadIdx.x == 0) nfound = 0u;
+  __syncthreads();
+  for (int item = blockIdx.x * (STAGE_BLOCK / WAVE) + threadIdx.x / WAVE; item < B.total_check; item += step) {
+    const int p = __builtin_amdgcn_readfirstlane(B.check_prob[item]);   // the wavefront's: its record in scalar registers
+    const ProbDesc D = B.descs[p];
+    const int k = (item - B.check_start[p]) * WAVE + lane;
+    bool need = false;
+    if (k < D.n) {
       switch (D.kind) {
         case KIND_ARROW:
-        case KIND_HERM: check_kind<KIND_ARROW>(D, opt, G, k0, lane); break;   // HERM: the real arrowhead on |z|
-        case KIND_DPR1: check_kind<KIND_DPR1>(D, opt, G, k0, lane); break;
-        default: check_kind<KIND_SVD>(D, opt, G, k0, lane); break;
+        case KIND_HERM: need = check_body<KIND_ARROW, 1, false, DEFER_WAVE>(D, opt, k, 0); break;   // HERM: the real arrowhead on |z|
+        case KIND_DPR1: need = check_body<KIND_DPR1, 1, false, DEFER_WAVE>(D, opt, k, 0); break;
+        default: need = check_body<KIND_SVD, 1, false, DEFER_WAVE>(D, opt, k, 0); break;
       }
+    }
+    const uint64_t mask = __ballot(need);
+    if (mask) {
+      const uint32_t more = (uint32_t)__popcll(mask);
+      uint32_t at = 0, room = 0;
+      if (lane == 0) at = atomicAdd(&nfound, more);
+      at = __builtin_amdgcn_readfirstlane(at);
+      room = at < CHECK_FOUND ? CHECK_FOUND - at : 0u;
+      uint32_t far = 0;   // the rest, past the block's room, straight to the list
+      if (lane == 0 && more > room) far = atomicAdd(&B.counters[1], more - room);
+      far = __builtin_amdgcn_readfirstlane(far);
+      const uint32_t mine = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+      if (need) {   // at most one entry per eigenvalue: the list has room for all
+        const uint2 e = make_uint2((unsigned)p, (unsigned)k);
+        if (mine < room) found[at + mine] = e;
+        else B.redo[far + (mine - room)] = e;
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t count = min(nfound, (uint32_t)CHECK_FOUND);
+  if (threadIdx.x == 0 && count > 0u) base = atomicAdd(&B.counters[1], count);
+  __syncthreads();
+  for (uint32_t q = threadIdx.x; q < count; q += STAGE_BLOCK) B.redo[base + q] = found[q];
+}
+
+// The plan's list, a wavefront per eigenvalue in turn, on all its lanes whatever
+// the batch (so a problem gives the same bits alone or in any batch).
+__global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_b_remedy(BatchArgs B,
+                                                                                                  Options opt) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const uint32_t count = B.counters[1];
+  const uint32_t step = gridDim.x * (STAGE_BLOCK / WAVE);
+  for (uint32_t q = blockIdx.x * (STAGE_BLOCK / WAVE) + threadIdx.x / WAVE; q < count; q += step) {
+    const uint2 e = B.redo[q];
+    const ProbDesc D = B.descs[__builtin_amdgcn_readfirstlane(e.x)];
+    const int k = __builtin_amdgcn_readfirstlane(e.y);
+    switch (D.kind) {
+      case KIND_ARROW:
+      case KIND_HERM: check_body<KIND_ARROW, WAVE, false, DEFER_NEAR_ZERO>(D, opt, k, lane); break;
+      case KIND_DPR1: check_body<KIND_DPR1, WAVE, false, DEFER_NEAR_ZERO>(D, opt, k, lane); break;
+      default: check_body<KIND_SVD, WAVE, false, DEFER_NEAR_ZERO>(D, opt, k, lane); break;
     }
   }
 }
 
 // The repairs the check stage deferred (each problem keeps its own list in its
-// workspace, as in the single-problem path): `per` blocks of REPAIR_BLOCK
-// lanes per problem stride over that problem's list, each listed eigenvalue
-// run by a whole block.  Blocks beyond a problem's list length skip the repairs.
+// workspace): `per` turns of REPAIR_BLOCK lanes per problem stride over that
+// problem's list, each listed eigenvalue run by a whole block.  Most problems list
+// nothing, so a block asks `group` turns at once, a lane each, and runs those with
+// work (a block a turn was 10,000 dispatches for the 10,000-problem plan, a turn
+// after the other 110 us of dependent loads).
 constexpr int REPAIR_BLOCK = 256;
+constexpr int REPAIR_GROUP = 64;   // most turns asked at once: a ballot's
 
-__global__ __launch_bounds__(REPAIR_BLOCK) void k_b_repair(BatchArgs B, Options opt, int per) {
-  const int p = (int)blockIdx.x / per;
-  const int x = (int)blockIdx.x - p * per;
-  const ProbDesc D = B.descs[p];
-  const Ws w = ws_view(D.ws, D.n);
-  const uint32_t c = min(*repair_count(w), (uint32_t)D.n);
-  const uint32_t* list = repair_list(w, D.n);
-  for (uint32_t q = (uint32_t)x; q < c; q += (uint32_t)per) {
-    const int k = (int)list[q];
-    if (k < 0 || k >= D.n) continue;
-    switch (D.kind) {
-      case KIND_ARROW:
-      case KIND_HERM: check_body<KIND_ARROW, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
-      case KIND_DPR1: check_body<KIND_DPR1, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
-      default: check_body<KIND_SVD, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
+__global__ __launch_bounds__(REPAIR_BLOCK) void k_b_repair(BatchArgs B, Options opt, int per, int group) {
+  __shared__ uint64_t work;
+  const int64_t turns = (int64_t)B.count * per;
+  for (int64_t base = (int64_t)blockIdx.x * group; base < turns; base += (int64_t)gridDim.x * group) {
+    if (threadIdx.x < WAVE) {
+      bool any = false;
+      if ((int)threadIdx.x < group && base + threadIdx.x < turns) {
+        const ProbDesc& D = B.descs[(base + threadIdx.x) / per];
+        const Ws w = ws_view(D.ws, D.n);
+        any = *repair_count(w) > 0u || (D.kind == KIND_ARROW && deflated_count(w) > 0);
+      }
+      const uint64_t mask = __ballot(any);
+      if (threadIdx.x == 0) work = mask;
+    }
+    __syncthreads();
+    uint64_t mask = work;
+    __syncthreads();
+    for (; mask; mask &= mask - 1) {
+      const int64_t turn = base + __builtin_ctzll(mask);
+      const int p = (int)(turn / per);
+      const int x = (int)(turn - (int64_t)p * per);
+      const ProbDesc D = B.descs[p];
+      const Ws w = ws_view(D.ws, D.n);
+      const uint32_t c = min(*repair_count(w), (uint32_t)D.n);
+      const uint32_t* list = repair_list(w, D.n);
+      for (uint32_t q = (uint32_t)x; q < c; q += (uint32_t)per) {
+        const int k = (int)list[q];
+        if (k < 0 || k >= D.n) continue;
+        switch (D.kind) {
+          case KIND_ARROW:
+          case KIND_HERM: check_body<KIND_ARROW, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
+          case KIND_DPR1: check_body<KIND_DPR1, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
+          default: check_body<KIND_SVD, REPAIR_BLOCK>(D, opt, k, threadIdx.x); break;
+        }
+      }
+      // a deflated arrowhead: the last of its `per` turns places the deflated eigenpairs
+      if (D.kind == KIND_ARROW && deflated_count(w) > 0) place_deflated_last(D, w, (uint32_t)per);
     }
   }
-  // a deflated arrowhead: the last of its `per` blocks places the deflated eigenpairs
-  if (D.kind == KIND_ARROW && deflated_count(w) > 0) place_deflated_last(D, w, (uint32_t)per);
 }
 
 template <int KIND>
@@ -396,7 +435,7 @@ __global__ __launch_bounds__(BLOCK) void k_b_counters(BatchArgs B, long long* ou
 // a launch whose start and end events, when given, are stamped by the dispatch itself
 template <typename F, typename... Args>
 void launch_ev(F kern, dim3 grid, dim3 block, hipStream_t st, hipEvent_t e0, hipEvent_t e1, Args... args) {
-  if (e0) hipExtLaunchKernelGGL(kern, grid, block, 0u, st, e0, e1, 0u, args...);
+  if (e0 || e1) hipExtLaunchKernelGGL(kern, grid, block, 0u, st, e0, e1, 0u, args...);
   else hipLaunchKernelGGL(kern, grid, block, 0, st, args...);
 }
 
@@ -410,20 +449,22 @@ struct arrow_batch_s {
   int64_t count;
   int flags;
   int32_t total_items, total_vec;
-  int repair_per;       // k_b_repair blocks per problem
+  int repair_per;       // k_b_repair turns per problem
+  int repair_group;     // ... and turns a block asks at once
   Options opt;          // the handle's options when the plan was created
   void* dev;            // device block: counters, descriptors, tables, workspaces
   int own_dev;          // dev allocated by the plan
   size_t dev_bytes;
   std::vector<ProbDesc> descs;
   std::vector<int32_t> tabs;   // item_start (count+1), lanes (count), vec_start (count+1), vec_mode (count),
-                               // check_start (count+1), check_lanes (count), vec_prob (one per vector tile)
+                               // check_start (count+1), vec_prob (one per vector tile), check_prob (one per
+                               // check-stage item)
   BatchArgs args;
-  int persistent_blocks;
+  int persistent_blocks, check_blocks, remedy_blocks, repair_blocks;
   hipGraph_t graph;
   hipGraphExec_t exec;
   int captured;
-  hipEvent_t ev[10];    // ARROW_BATCH_TIMING: start and end of each of the five kernels
+  hipEvent_t ev[10];    // ARROW_BATCH_TIMING: start and end of each of the five stages
   int ev_made;
   int timed_runs;
   uint32_t magic;
@@ -446,19 +487,25 @@ static int64_t vec_tiles(const arrow_desc_t& a) {
 }
 
 struct Layout {
-  size_t off_desc, off_tab, off_ws, total;
-  int64_t vec_total;
+  size_t off_desc, off_tab, off_redo, off_ws, total;
+  int64_t vec_total, check_total, pairs;
 };
 
 static Layout plan_layout(int64_t count, const arrow_desc_t* descs) {
   Layout L;
-  L.vec_total = 0;
-  for (int64_t p = 0; p < count; ++p) L.vec_total += vec_tiles(descs[p]);
+  L.vec_total = L.check_total = L.pairs = 0;
+  for (int64_t p = 0; p < count; ++p) {
+    L.vec_total += vec_tiles(descs[p]);
+    L.check_total += (descs[p].n + WAVE - 1) / WAVE;
+    L.pairs += descs[p].n;
+  }
   size_t off = 256;                                   // counters
   L.off_desc = off;
   off = align_up(off + (size_t)count * sizeof(ProbDesc), 256);
   L.off_tab = off;
-  off = align_up(off + (size_t)(6 * count + 3 + L.vec_total) * sizeof(int32_t), 256);
+  off = align_up(off + (size_t)(5 * count + 3 + L.vec_total + L.check_total) * sizeof(int32_t), 256);
+  L.off_redo = off;
+  off = align_up(off + (size_t)L.pairs * sizeof(uint2), 256);
   L.off_ws = off;
   for (int64_t p = 0; p < count; ++p) off += align_up(ws_doubles(descs[p].n) * sizeof(double), 256);
   L.total = off;
@@ -527,7 +574,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   }
   DeviceGuard g(h->device);
   const Layout L = plan_layout(count, descs);
-  if (L.vec_total > INT32_MAX / 2) return -2;
+  if (L.vec_total > INT32_MAX / 2 || L.check_total > INT32_MAX / 2 || L.pairs > INT32_MAX) return -2;
   if (workspace && workspace_bytes < L.total) return -8;
   arrow_batch_s* b = new (std::nothrow) arrow_batch_s();
   if (!b) return ARROW_ERR_NOMEM;
@@ -552,14 +599,14 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   std::stable_sort(order.begin(), order.end(),
                    [&](int64_t a, int64_t c) { return descs[a].n > descs[c].n; });
   b->descs.resize((size_t)count);
-  b->tabs.assign((size_t)(6 * count + 3 + L.vec_total), 0);
+  b->tabs.assign((size_t)(5 * count + 3 + L.vec_total + L.check_total), 0);
   int32_t* item_start = b->tabs.data();
   int32_t* lanes = item_start + count + 1;
   int32_t* vec_start = lanes + count;
   int32_t* vec_mode = vec_start + count + 1;
   int32_t* check_start = vec_mode + count;
-  int32_t* check_lanes = check_start + count + 1;
-  int32_t* vec_prob = check_lanes + count;
+  int32_t* vec_prob = check_start + count + 1;
+  int32_t* check_prob = vec_prob + L.vec_total;
   char* base = (char*)b->dev;
   size_t wsoff = L.off_ws;
   int64_t items = 0, vchunks = 0, citems = 0;
@@ -585,10 +632,8 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
     lanes[q] = G;
     item_start[q] = (int32_t)items;
     items += (a.n + (WAVE / G) - 1) / (WAVE / G);
-    const int Gc = b->opt.check_lanes ? b->opt.check_lanes : G;
-    check_lanes[q] = Gc;
     check_start[q] = (int32_t)citems;
-    citems += (a.n + (WAVE / Gc) - 1) / (WAVE / Gc);
+    for (int64_t t = (a.n + WAVE - 1) / WAVE; t > 0; --t) check_prob[citems++] = (int32_t)q;
     vec_start[q] = (int32_t)vchunks;
     if (D.V && a.kind == ARROW_KIND_HERM) {
       vec_mode[q] = 1;
@@ -606,7 +651,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   item_start[count] = (int32_t)items;
   vec_start[count] = (int32_t)vchunks;
   check_start[count] = (int32_t)citems;
-  if (items > INT32_MAX / 2 || vchunks > INT32_MAX / 2 || citems > INT32_MAX / 2) {
+  if (items > INT32_MAX / 2) {
     if (b->own_dev) (void)hipFree(b->dev);
     delete b;
     return -2;
@@ -630,8 +675,9 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   A.vec_start = A.lanes + count;
   A.vec_mode = A.vec_start + count + 1;
   A.check_start = A.vec_mode + count;
-  A.check_lanes = A.check_start + count + 1;
-  A.vec_prob = A.check_lanes + count;
+  A.vec_prob = A.check_start + count + 1;
+  A.check_prob = A.vec_prob + L.vec_total;
+  A.redo = (uint2*)(base + L.off_redo);
   A.total_check = (int32_t)citems;
   A.counters = (uint32_t*)base;
   A.count = (int32_t)count;
@@ -640,6 +686,14 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   const int64_t want = (int64_t)h->cus * 4 * ROOT_WAVES * WAVE / STAGE_BLOCK;
   const int64_t need = ((int64_t)items * WAVE + STAGE_BLOCK - 1) / STAGE_BLOCK;
   b->persistent_blocks = (int)std::max<int64_t>(1, std::min(want, need));
+  A.chunk = items >= CHUNK_FROM * want * (STAGE_BLOCK / WAVE) ? ROOT_CHUNK : 1;
+  // one item a wavefront, eight blocks a compute unit at most; remedies and repairs are few
+  const int64_t citem_blocks = (citems + STAGE_BLOCK / WAVE - 1) / (STAGE_BLOCK / WAVE);
+  b->check_blocks = (int)std::min<int64_t>(8 * (int64_t)h->cus, citem_blocks);
+  b->remedy_blocks = (int)std::min<int64_t>(4 * (int64_t)h->cus, (L.pairs + STAGE_BLOCK / WAVE - 1) / (STAGE_BLOCK / WAVE));
+  const int64_t turns = count * b->repair_per;
+  b->repair_group = (int)std::min<int64_t>(REPAIR_GROUP, (turns + 4 * (int64_t)h->cus - 1) / (4 * (int64_t)h->cus));
+  b->repair_blocks = (int)std::min<int64_t>(4 * (int64_t)h->cus, (turns + b->repair_group - 1) / b->repair_group);
   if ((flags & ARROW_BATCH_TIMING) && !(flags & ARROW_BATCH_GRAPH)) {
     b->ev_made = 1;
     for (int e = 0; e < 10; ++e)
@@ -657,9 +711,10 @@ static int batch_launch(arrow_batch_s* b, hipStream_t st) {
   auto ev = [&](int e) -> hipEvent_t { return tm ? b->ev[e] : nullptr; };
   launch_ev(k_b_prep, dim3((unsigned)b->count), dim3(BLOCK), st, ev(0), ev(1), A);
   launch_ev(k_b_root, dim3((unsigned)b->persistent_blocks), dim3(STAGE_BLOCK), st, ev(2), ev(3), A, opt);
-  launch_ev(k_b_check, dim3((unsigned)b->persistent_blocks), dim3(STAGE_BLOCK), st, ev(4), ev(5), A, opt);
-  launch_ev(k_b_repair, dim3((unsigned)(b->count * b->repair_per)), dim3(REPAIR_BLOCK), st, ev(6), ev(7), A, opt,
-            b->repair_per);
+  launch_ev(k_b_check, dim3((unsigned)b->check_blocks), dim3(STAGE_BLOCK), st, ev(4), hipEvent_t(nullptr), A, opt);
+  launch_ev(k_b_remedy, dim3((unsigned)b->remedy_blocks), dim3(STAGE_BLOCK), st, hipEvent_t(nullptr), ev(5), A, opt);
+  launch_ev(k_b_repair, dim3((unsigned)b->repair_blocks), dim3(REPAIR_BLOCK), st, ev(6), ev(7), A, opt,
+            b->repair_per, b->repair_group);
   if (b->total_vec > 0) launch_ev(k_b_vec, dim3((unsigned)b->total_vec), dim3(BLOCK), st, ev(8), ev(9), A);
   else if (tm) { (void)hipEventRecord(b->ev[8], st); (void)hipEventRecord(b->ev[9], st); }
   if (tm) b->timed_runs += 1;

@@ -547,9 +547,9 @@ __host__ __device__ inline void root_body(const ProbDesc& D, const Options& opt,
 // listed (its exact sum of f(0) runs on whole blocks); Remark 2 and the DPR1
 // re-measure run here on the caller's G lanes, as the first pass does.  DEFER =
 // DEFER_WAVE: Remark 1 is listed as for DEFER_NEAR_ZERO; an eigenvalue that needs
-// Remark 2 or the DPR1 re-measure writes nothing and makes the call return true,
-// and the caller runs check_body on it again (DEFER_NEAR_ZERO) with all lanes of
-// its wavefront.  Every other call returns false.
+// Remark 2, the DPR1 re-measure or a norm pass writes nothing and makes the call
+// return true, and the caller runs check_body on it again (DEFER_NEAR_ZERO) with
+// all lanes of a wavefront.  Every other call returns false.
 // The list reuses the sort's rank array, free once the poles are sorted; its
 // length sits in hdr[6] and is cleared by the prologue.
 
@@ -762,8 +762,10 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
   // the first pass's norm holds while its shift and mu stand (no remedy)
   const double nr1 = w.nr1[k];
   const bool first = pv == w.pv1[k] && s == 0.0 && mu == w.mu1[k] && nr1 == nr1;
-  if constexpr (ASK) {
+  if constexpr (ASK || DEFER == DEFER_WAVE) {
     if (!first) return true;
+  }
+  if constexpr (ASK) {
     if (!commit) return false;
   }
   const double inrm = first ? nr1 : (rn == rn ? rn : inv_norm<KIND, G>(P, pv, s, mu, ln, off_hint));
@@ -791,8 +793,10 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
       }
     }
     w.pv[col] = pv;
-    w.kbc[col] = w.kb1[k];
-    w.knu[col] = knu_out;
+    if constexpr (DEFER == DEFER_NONE || DEFER == DEFER_BLOCK) {   // single problems' outputs (and the rare repair)
+      w.kbc[col] = w.kb1[k];
+      w.knu[col] = knu_out;
+    }
     w.sf[col] = s;
     w.mu[col] = mu;
     // q = (D - lambda)^{-1} u for rho < 0 is minus the vector of (-D) + |rho| u u^T
