@@ -315,7 +315,9 @@ int arrow_solve_batched(arrow_handle_t h, int64_t count, const arrow_desc_t* des
  *   scope ARROW_SCHEDULE_SINGLE: arrow_eig / dpr1_eig / arrow_svd calls;
  *     lanes 1, 2, 4, ..., 64.  n beyond the table and entries = 0 use the
  *     built-in rule (about 8 pole terms per lane, at most 64 lanes).  The
- *     option ARROW_OPT_LANES, when nonzero, overrides the table.
+ *     option ARROW_OPT_LANES, when nonzero, overrides the table.  From n = 4609
+ *     while the poles fit a compute unit's LDS (n to about 20200) a kernel of its
+ *     own takes 64 lanes whatever the table says, unless that option is set.
  *   scope ARROW_SCHEDULE_BATCH: plans created afterwards; lanes 4, ..., 64;
  *     n beyond the table uses 64; entries = 0 restores the built-in table
  *     {24: 4, 48: 8, 96: 16, 192: 32, larger: 64}.
@@ -341,7 +343,8 @@ int arrow_set_lanes_table(arrow_handle_t h, int scope, int32_t entries, const in
  *   between launches): front (up to 16384 poles), root and vectors are their
  *   kernels' durations, sort and check the time between them.  Up to n = 1280 one
  *   kernel does check and vectors, and counts as vectors; without vectors, the
- *   last kernel of the check does.  The five sum to the call up to the end of that
+ *   last kernel of the check does.  From n = 4609 while the poles fit a compute
+ *   unit's LDS (n to about 20200) root writes most of the vectors itself.  The five sum to the call up to the end of that
  *   kernel.  Needs ARROW_OPT_TIMING set before that call; waits for it to finish.
  *   Returns ARROW_ERR_STATE when no timed call exists.
  * arrow_timing_of: the same for the most recent timed call (age 0) or the one

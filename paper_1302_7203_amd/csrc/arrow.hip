@@ -69,6 +69,8 @@ constexpr int PREP_MAX = 16384;   // the blocks' order checks read n^2 / 64 keys
 constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (its rank is none)
 
 __host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
+// 1 when the caller's poles already are in the sorted order
+__host__ __device__ inline uint32_t* in_order(const Ws& w) { return (uint32_t*)(w.hdr + 11); }
 
 template <int KIND, bool ONE>
 __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* __restrict__ poles, int groups) {
@@ -180,6 +182,7 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     for (int q = threadIdx.x; q < ms; q += PREP_BLOCK)
       for (int l = 0; l < ms; ++l) dup |= l != q && key(poles[l]) == key(poles[q]);
   }
+  if (threadIdx.x == 0) *in_order(w) = down ? 0u : 1u;
   prologue_reduce<KIND, PREP_BLOCK>(D, w, acc, (st & ~ST_NAN) | (dup ? INFO_REDUCIBLE : 0u), zp);
 }
 
@@ -212,6 +215,7 @@ __global__ __launch_bounds__(FRONT_BLOCK) void k_front(ProbDesc D) {
   up = __syncthreads_or(up);
   const bool rev = down && !up;   // strictly increasing: sorted index ms-1-j
   const int bad = down && up;
+  if (threadIdx.x == 0) *in_order(w) = down ? 0u : 1u;
   if (bad) {
     uint32_t* rank = rank_array(w, D.n);
     for (int j = threadIdx.x; j < ms; j += FRONT_BLOCK) rank[j] = 0;
@@ -426,18 +430,24 @@ __device__ inline void finish_rows(const ProbDesc& D, int rt, int nc, const FinS
   }
 }
 
+// output column of the finished eigenvalue k, -1 past a deflated problem's order
+template <int KIND>
+__device__ inline int finish_col(const ProbDesc& D, const Ws& w, int k) {
+  if constexpr (KIND == KIND_ARROW) {
+    const int nd = deflated_count(w);
+    if (nd > 0) return (k <= reduced_m(w)) ? k + count_above(w.dv, nd, w.lr[k], false) : -1;
+  }
+  if constexpr (KIND == KIND_DPR1) {
+    if (D.neg) return D.n - 1 - k;
+  }
+  return k;
+}
+
 // column data of the finished eigenvalue k into slot c (its final shift pair is
 // in the workspace)
 template <int KIND>
 __device__ inline void finish_stage(const ProbDesc& D, const Ws& w, int k, int c, FinStage& L) {
-  int col = k;
-  if constexpr (KIND == KIND_ARROW) {
-    const int nd = deflated_count(w);
-    if (nd > 0) col = (k <= reduced_m(w)) ? k + count_above(w.dv, nd, w.lr[k], false) : -1;
-  }
-  if constexpr (KIND == KIND_DPR1) {
-    if (D.neg) col = D.n - 1 - k;
-  }
+  const int col = finish_col<KIND>(D, w, k);
   L.col[c] = col;
   if (col < 0) return;
   L.pv[c] = w.pv[col];
@@ -526,6 +536,276 @@ __global__ __launch_bounds__(BLOCK) void k_vec(ProbDesc D, int row_tiles, int co
   if ((int)threadIdx.x < nc) finish_stage<KIND>(D, w, k0 + threadIdx.x, threadIdx.x, L);
   __syncthreads();
   finish_rows<KIND, W, RPT>(D, blockIdx.x - ct * row_tiles, nc, L);
+}
+
+__device__ inline double from_lane(double v, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
+                          __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+
+// The columns that the lanes of `mask` hold (output column, shift pair, 1/||x||,
+// sigma), by one wavefront: COL_ROWS rows a lane at a time, loaded together, then
+// every column's entries from them.  W rows a store (2: 16-byte stores, n and the
+// leading dimensions even).  ds: the poles in the caller's row order in LDS, or null
+// (read from the caller's array).  The values are vec_entry's; its tests are taken
+// out of the entries, which share the wavefronts' issue slots with the root stage:
+// the corner row is written on its own, a zero shaft entry occurs only in a deflated
+// problem (zeros), and an offset of 0 (all but Remark 2(b)) is not subtracted.
+constexpr int COL_ROWS = 8;
+
+template <int KIND, int W>
+__device__ __forceinline__ void wave_columns(const ProbDesc& D, uint64_t mask, int col, double pv, double s, double mu,
+                                             double inrm, double sig, int lane, const double* ds, bool zeros) {
+  constexpr int R = COL_ROWS, PER = R / W;
+  constexpr bool CPLX = KIND == KIND_HERM;
+  const int n = D.n;
+  const int body = (KIND == KIND_DPR1) ? n : n - 1;   // rows of the formula; the corner row is the last one else
+  for (int base = 0; base < n; base += 64 * R) {
+    double dr[R], num[R], im[CPLX ? R : 1];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int r = base + (q / W) * 64 * W + lane * W + q % W;
+      const bool in = r < body;
+      dr[q] = in ? (ds ? ds[r] : in_pole<KIND>(D, r)) : 0.0;
+      num[q] = in ? D.z[CPLX ? 2 * r : r] : 0.0;
+      if constexpr (CPLX) im[q] = in ? D.z[2 * r + 1] : 0.0;
+      if constexpr (KIND == KIND_SVD) num[q] *= dr[q];
+    }
+    for (uint64_t left = mask; left; left &= left - 1) {
+      const int src = __builtin_ctzll(left);
+      const size_t c = (size_t)__builtin_amdgcn_readlane(col, src);
+      const double cpv = from_lane(pv, src), cs = from_lane(s, src), cmu = from_lane(mu, src), ci = from_lane(inrm, src);
+      const double csig = (KIND == KIND_SVD) ? from_lane(sig, src) : 0.0;
+      double* vc = D.V + c * (size_t)D.ldv * (CPLX ? 2 : 1);
+      double* uc = (KIND == KIND_SVD && D.U) ? D.U + c * (size_t)D.ldu : nullptr;
+      double f[R];   // 1 / ((d_r - pole - s) - mu)
+      if (cs == 0.0) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) f[q] = recip(pdiff<KIND>(dr[q], cpv) - cmu);
+      } else {
+#pragma unroll
+        for (int q = 0; q < R; ++q) f[q] = recip((pdiff<KIND>(dr[q], cpv) - cs) - cmu);
+      }
+#pragma unroll
+      for (int q = 0; q < PER; ++q) {
+        const int r = base + q * 64 * W + lane * W;
+        if (r >= n) continue;   // W = 2: n is even, so r + 1 < n as well
+        auto value = [&](int e, int row) {
+          if (KIND != KIND_DPR1 && row >= body) return -ci;
+          if (KIND == KIND_ARROW && zeros && num[e] == 0.0) return 0.0;
+          return (num[e] * ci) * f[e];
+        };
+        if constexpr (CPLX) {
+          const v2d u = {r < body ? (num[q] * ci) * f[q] : -ci, r < body ? (im[q] * ci) * f[q] : 0.0};
+          __builtin_nontemporal_store(u, (v2d*)vc + r);
+        } else if constexpr (W == 1) {
+          const double v = value(q, r);
+          __builtin_nontemporal_store(v, vc + r);
+          if (KIND == KIND_SVD && uc) __builtin_nontemporal_store(svd_left(D, csig, v, r), uc + r);
+        } else {
+          const v2d vv = {value(2 * q, r), value(2 * q + 1, r + 1)};
+          __builtin_nontemporal_store(vv, (v2d*)(vc + r));
+          if (KIND == KIND_SVD && uc) {
+            const v2d uu = {svd_left(D, csig, vv.x, r), svd_left(D, csig, vv.y, r + 1)};
+            __builtin_nontemporal_store(uu, (v2d*)(uc + r));
+          }
+        }
+      }
+    }
+  }
+}
+
+// Root stage and vectors of a large problem (n > BIG_MIN) in one launch.  A block
+// of BIG_BLOCK threads (a compute unit's, with the staged arrays) takes `each`
+// consecutive eigenvalues; its wavefronts take them one by one, all 64 lanes each,
+// and an eigenvalue whose neighbours' first passes are done too is tested and
+// output by whichever wavefront completes the three; its column waits in LDS.  At
+// most BIG_WRITERS wavefronts at a time write waiting columns, BIG_TAKE a sweep,
+// so that the stores run while the others compute (all 16 would write together,
+// since they compute in step); when the eigenvalues are taken, all do.  Nobody
+// waits: the wavefront that adds the last column finds it.
+// Left for the launches behind it (BigTail): the first and last eigenvalue of each
+// block, whose neighbours are another block's, and those that need a repair.
+//
+// HOT 1: poles and weights in LDS; HOT 2: the poles alone, where both do not fit.
+// At n = 16384 the root stage was bound by the L2: 72 bytes a term, 860 us at 22
+// TB/s; with the poles in LDS 40 bytes, and bound by issued instructions, 603 us
+// (n = 8192 285 -> 209 us, 5000 120 -> 101 us).  With the columns 875 us, where
+// root stage and vectors took 860 + 387: a writing wavefront is one fewer computing
+// (two or eight writers at a time: 900 and 920 us).
+constexpr int BIG_BLOCK = 1024;
+constexpr int BIG_MIN = 4608;              // below, k_root's smaller blocks spread better: 4096 graded 67 us against 82
+constexpr int BIG_EACH = BIG_BLOCK / 64;   // fewest eigenvalues a block takes
+#ifndef AHD_BIG_WRITERS
+#define AHD_BIG_WRITERS 4
+#endif
+constexpr int BIG_WRITERS = AHD_BIG_WRITERS;
+constexpr int BIG_TAKE = 4;
+
+struct BigCol {   // a waiting column
+  double pv, sf, mu, inrm, sig;
+  int col;
+  int done;       // first passes done of the eigenvalue and its neighbours
+};
+
+static size_t big_lds(int each) { return (size_t)each * sizeof(BigCol) + (size_t)((each + 31) / 32) * sizeof(uint32_t); }
+
+template <int KIND, int HOT>
+__global__ __launch_bounds__(BIG_BLOCK) void k_root_big(ProbDesc D, Options opt, int each, bool pair) {
+  constexpr int SK = (KIND == KIND_HERM) ? KIND_ARROW : KIND;
+  extern __shared__ double lds[];
+  __shared__ int next, writers;
+  const Ws w = ws_view(D.ws, D.n);
+  const int ns = sorted_count(D);
+  BigCol* cols = (BigCol*)(lds + (HOT == 1 ? ns + D.n - 1 : ns));
+  uint32_t* waiting = (uint32_t*)(cols + each);   // a bit per column
+  const int words = (each + 31) / 32;
+  const int k0 = (int)blockIdx.x * each, k1 = min(D.n, k0 + each);
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) {
+    next = k0;
+    writers = 0;
+  }
+  for (int q = threadIdx.x; q < each; q += BIG_BLOCK) cols[q].done = 0;
+  for (int q = threadIdx.x; q < words; q += BIG_BLOCK) waiting[q] = 0u;
+  if constexpr (HOT == 1) {
+    stage_hot(D, lds);
+  } else {
+    for (int j = threadIdx.x; j < ns; j += BIG_BLOCK) lds[j] = w.ds[j];
+    __syncthreads();
+  }
+  const bool zeros = KIND == KIND_ARROW && deflated_count(w) > 0;
+  const double* rows = (*in_order(w) && !zeros) ? lds : nullptr;
+  const bool vec = D.V != nullptr;
+  // one sweep over up to BIG_TAKE waiting columns; false when there are none
+  auto write_some = [&]() -> bool {
+    uint32_t got = 0u;
+    int at = 0;
+    if (lane == 0) {
+      for (; at < words; ++at) {
+        uint32_t pick = 0u, have = waiting[at];
+        for (int q = 0; q < BIG_TAKE && have; ++q) {
+          pick |= have & (0u - have);
+          have &= have - 1u;
+        }
+        if (pick) got = atomicAnd(&waiting[at], ~pick) & pick;
+        if (got) break;
+      }
+    }
+    got = __builtin_amdgcn_readfirstlane(got);
+    if (!got) return false;
+    at = __builtin_amdgcn_readfirstlane(at);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    const int count = __popc(got);
+    uint32_t left = got;
+    for (int q = 0; q < lane && q < count - 1; ++q) left &= left - 1u;   // lane q: the q-th column
+    const BigCol c = cols[32 * at + __ffs(left) - 1];
+    const uint64_t mask = (1ull << count) - 1ull;
+    if (KIND != KIND_HERM && pair)
+      wave_columns<KIND, KIND == KIND_HERM ? 1 : 2>(D, mask, c.col, c.pv, c.sf, c.mu, c.inrm, c.sig, lane, rows, zeros);
+    else wave_columns<KIND, 1>(D, mask, c.col, c.pv, c.sf, c.mu, c.inrm, c.sig, lane, rows, zeros);
+    return true;
+  };
+  for (;;) {
+    int k = 0;
+    if (lane == 0) k = atomicAdd(&next, 1);
+    k = __builtin_amdgcn_readfirstlane(k);
+    const bool more = k < k1;
+    if (more) {
+      root_body<SK, 64, HOT>(D, opt, k, lane, lds, lds + ns);
+      // lanes 0..2: k - 1, k and k + 1 have one more first pass
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      const int q = k - 1 + lane;
+      bool ready = false;
+      if (lane < 3 && q >= k0 && q < k1) {
+        const int need = 1 + (q > 0 ? 1 : 0) + (q < D.n - 1 ? 1 : 0);   // at a block's edge never reached
+        ready = atomicAdd(&cols[q - k0].done, 1) + 1 == need;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      if (ready) {
+        if (check_body<SK, 1, false, DEFER_BLOCK>(D, opt, q, 0)) {
+          defer_repair(w, D.n, q, 0);
+        } else if (vec) {
+          const int col = finish_col<KIND>(D, w, q);
+          if (col >= 0) {   // this lane wrote them
+            BigCol& c = cols[q - k0];
+            c.col = col;
+            c.pv = w.pv[col];
+            c.sf = w.sf[col];
+            c.mu = w.mu[col];
+            c.inrm = w.inrm[col];
+            c.sig = (KIND == KIND_SVD) ? D.lam[col] : 0.0;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            atomicOr(&waiting[(q - k0) >> 5], 1u << ((q - k0) & 31));
+          }
+        }
+      }
+    }
+    // all lanes together again before the next uniform test: without an operation
+    // that the compiler keeps convergent here, it may send the lanes that know the
+    // test's outcome from above (no vectors) straight round the loop, whose head then
+    // reads lane 0 without lane 0
+    __builtin_amdgcn_wave_barrier();
+    if (!more) break;
+    if (vec) {
+      int place = 0;
+      if (lane == 0) place = atomicAdd(&writers, 1);
+      if (__builtin_amdgcn_readfirstlane(place) < BIG_WRITERS) write_some();
+      if (lane == 0) atomicSub(&writers, 1);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // every eigenvalue is taken: what waits, and what this wavefront added
+  if (vec)
+    while (write_some()) __builtin_amdgcn_wave_barrier();
+}
+
+// What k_root_big leaves: index e of a block's edge eigenvalue, or -1 where the
+// problem's own end makes it no edge
+struct BigTail {
+  int each, blocks;
+  __device__ int edge(int e, int n) const {
+    const int b = e >> 1;
+    if (e & 1) return b + 1 < blocks ? (b + 1) * each - 1 : -1;
+    return b > 0 ? b * each : -1;
+  }
+};
+
+// the test and outputs of the edges, one lane each
+template <int KIND>
+__global__ __launch_bounds__(CHECK_BLOCK) void k_check_edges(ProbDesc D, Options opt, BigTail T) {
+  const int e = (int)(blockIdx.x * CHECK_BLOCK + threadIdx.x);
+  if (e >= 2 * T.blocks) return;
+  const int k = T.edge(e, D.n);
+  if (k < 0) return;
+  if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0)) defer_repair(ws_view(D.ws, D.n), D.n, k, 0);
+}
+
+// the columns of the edges and of the repaired eigenvalues (an edge that was
+// repaired is written twice, with the same values), BLOCK * RPT rows of TAIL_COLS a turn
+constexpr int TAIL_COLS = 4;
+
+template <int KIND, int W, int RPT>
+__global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, BigTail T) {
+  __shared__ FinStage L;
+  const Ws w = ws_view(D.ws, D.n);
+  const int listed = (int)min(*repair_count(w), (uint32_t)D.n);
+  const uint32_t* list = repair_list(w, D.n);
+  const int total = 2 * T.blocks + listed;
+  const int turns = (total + TAIL_COLS - 1) / TAIL_COLS * row_tiles;
+  for (int turn = blockIdx.x; turn < turns; turn += gridDim.x) {
+    const int ct = turn / row_tiles, e0 = ct * TAIL_COLS;
+    const int nc = min(total - e0, TAIL_COLS);
+    if ((int)threadIdx.x < nc) {
+      const int e = e0 + threadIdx.x;
+      const int k = e < 2 * T.blocks ? T.edge(e, D.n) : (int)list[e - 2 * T.blocks];
+      if (k >= 0 && k < D.n) finish_stage<KIND>(D, w, k, threadIdx.x, L);
+      else L.col[threadIdx.x] = -1;
+    }
+    __syncthreads();
+    finish_rows<KIND, W, RPT>(D, turn - ct * row_tiles, nc, L);
+    __syncthreads();
+  }
 }
 
 // The deflated eigenpairs of a reducible arrowhead: placed among the solved ones,
@@ -646,15 +926,29 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
   }
   // the root and finish stages are timed by their kernels' own start and end;
   // the stages between take up the dispatch gaps
-  const int G = single_lanes(h, D.n);
   const size_t hot = (size_t)(ms + D.n - 1) * sizeof(double);
-  const size_t lds = (hot <= h->lds_max) ? hot : 0;
-  launch_root_any<SK>(G, D, h->opt, st, lds, at(2), at(3));
+  // the large problems' kernel, where at least the poles fit a compute unit's LDS
+  // and nobody asked for another number of lanes
+  const int each = (int)std::max<int64_t>(BIG_EACH, (D.n + h->cus - 1) / h->cus);
+  const size_t poles = (size_t)ms * sizeof(double), extra = big_lds(each) + 1024;   // and a little static LDS
+  const bool big = D.n > BIG_MIN && h->lanes == 0 && poles + extra <= h->lds_max;
+  const BigTail tail{each, (D.n + each - 1) / each};
+  const bool hot_both = hot + extra <= h->lds_max;
+  const bool pair_rows = KIND != KIND_HERM && (D.n % 2 == 0) && (D.ldv % 2 == 0) && (((uintptr_t)D.V & 15) == 0) &&
+                         (!D.U || ((D.ldu % 2 == 0) && (((uintptr_t)D.U & 15) == 0)));
+  if (big) {
+    const dim3 grid((unsigned)tail.blocks);
+    const size_t lds = (hot_both ? hot : poles) + big_lds(each);
+    if (hot_both) launch_timed(k_root_big<KIND, 1>, grid, dim3(BIG_BLOCK), lds, st, at(2), at(3), D, h->opt, each, pair_rows);
+    else launch_timed(k_root_big<KIND, 2>, grid, dim3(BIG_BLOCK), lds, st, at(2), at(3), D, h->opt, each, pair_rows);
+  } else {
+    const size_t lds = (hot <= h->lds_max) ? hot : 0;
+    launch_root_any<SK>(single_lanes(h, D.n), D, h->opt, st, lds, at(2), at(3));
+  }
   {
     const VecShape sh = vec_shape(D.n);
     // 16-byte stores: a complex entry each, or two rows where every column starts on 16 bytes
-    const bool pair = KIND != KIND_HERM && (D.n % 2 == 0) && (D.ldv % 2 == 0) && (((uintptr_t)D.V & 15) == 0) &&
-                      (!D.U || ((D.ldu % 2 == 0) && (((uintptr_t)D.U & 15) == 0)));
+    const bool pair = pair_rows;
     constexpr int W2 = KIND == KIND_HERM ? 1 : 2;
     auto by_shape = [&](auto&& go) {   // go(rows per store, rows per thread)
       using one = std::integral_constant<int, 1>;
@@ -673,8 +967,13 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
                        at(5), D, h->opt, redo_blocks, cols);
       });
     } else {
-      hipLaunchKernelGGL(k_check<SK>, dim3((unsigned)((D.n + CHECK_BLOCK - 1) / CHECK_BLOCK)), dim3(CHECK_BLOCK), 0, st,
-                         D, h->opt);
+      if (big) {
+        hipLaunchKernelGGL(k_check_edges<SK>, dim3((unsigned)((2 * tail.blocks + CHECK_BLOCK - 1) / CHECK_BLOCK)),
+                           dim3(CHECK_BLOCK), 0, st, D, h->opt, tail);
+      } else {
+        hipLaunchKernelGGL(k_check<SK>, dim3((unsigned)((D.n + CHECK_BLOCK - 1) / CHECK_BLOCK)), dim3(CHECK_BLOCK), 0,
+                           st, D, h->opt);
+      }
       const size_t lds_r = (hot + 4096 <= h->lds_max) ? hot : 0;   // the block reductions add a little static LDS
       const dim3 grid((unsigned)std::min<int64_t>(D.n, h->cus));
       hipEvent_t r0 = D.V ? nullptr : at(4), r1 = D.V ? nullptr : at(5);
@@ -684,6 +983,11 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
         by_shape([&](auto wd, auto rpt) {
           if constexpr (decltype(rpt)::value >= 4) {
             const int row_tiles = (int)((D.n + (int64_t)BLOCK * sh.rpt - 1) / ((int64_t)BLOCK * sh.rpt));
+            if (big) {
+              launch_timed(k_vec_tail<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(2 * h->cus)),
+                           dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, tail);
+              return;
+            }
             const int64_t chunks = (D.n + sh.cols - 1) / sh.cols;
             launch_timed(k_vec<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(row_tiles * chunks)),
                          dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, sh.cols);

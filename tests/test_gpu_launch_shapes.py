@@ -1,6 +1,7 @@
 """Single solves at the orders where their launches change: one block ranks up to 256
 poles alone, several above, the order check's own path above 16384; one launch finishes
-up to n = 1280, three above.  Bars: the oracle at 1e-13 on sampled eigenpairs, and bitwise
+up to n = 1280, three above; above 4608 root stage and vectors share a launch, with poles
+and weights in LDS to about n = 10150, the poles alone to about 20200, neither above.  Bars: the oracle at 1e-13 on sampled eigenpairs, and bitwise
 the same result however the poles are ordered."""
 import numpy as np
 import pytest
@@ -100,3 +101,57 @@ def test_equal_poles_and_bad_input_are_seen_in_any_order(n, oracle_lib):
     assert_close(out.lam.cpu().numpy()[ks], ref.lam, "reducible values")
     assert_close(out.V.cpu().numpy()[:, ks], ref.vec, "reducible vectors")
     assert np.array_equal((out.info.cpu().numpy()[ks] & 1024) != 0, ref.tau == 0)
+
+
+@pytest.mark.parametrize("kind,n", [(W.KIND_ARROW, 4608), (W.KIND_ARROW, 4609), (W.KIND_DPR1, 4613), (W.KIND_SVD, 4610),
+                                    (W.KIND_HERM, 4611), (W.KIND_DPR1, 5000), (W.KIND_SVD, 8193),
+                                    (W.KIND_ARROW, 10100), (W.KIND_DPR1, 10101), (W.KIND_ARROW, 10240)])
+def test_large_problems_in_any_order(kind, n, oracle_lib):
+    import torch
+    rng = np.random.default_rng(7000 * kind + n)
+    pr = _make(kind, n, rng)
+    if kind == W.KIND_DPR1 and n % 2:
+        pr.scalar = -pr.scalar
+    perm = np.argsort(-np.abs(pr.d) if kind == W.KIND_SVD else -pr.d, kind="stable")
+    srt = W.Problem(kind, n, pr.d[perm], pr.z[perm], pr.scalar)
+    base = _solve(srt)
+    # the first and last eigenvalues of the blocks (of at least 16) among the samples
+    _sampled(srt, base, count=40)
+    assert not bool(base.V.isnan().any())
+    q = rng.permutation(pr.d.size)
+    out = _solve(W.Problem(kind, n, srt.d[q], srt.z[q], srt.scalar))
+    assert torch.equal(out.lam, base.lam) and torch.equal(out.info, base.info)
+    rows = torch.from_numpy(np.concatenate([q, np.arange(q.size, n)])).to(base.V.device)
+    assert torch.equal(out.V, base.V[rows])
+    vals = _solve(srt, vectors=False)
+    assert torch.equal(vals.lam, base.lam) and torch.equal(vals.info, base.info)
+
+
+@pytest.mark.parametrize("n", [3001, 5000])
+def test_large_reducible_and_clustered(n, oracle_lib):
+    rng = np.random.default_rng(n)
+    red = W.reducible_arrow(n, rng, zero_frac=0.2, repeat_every=7)
+    out = _solve(red)
+    ks = np.arange(0, n, max(1, n // 60))
+    ref = oracle.arrow_eig(red.d, red.z, red.scalar, ks=ks)
+    assert_close(out.lam.cpu().numpy()[ks], ref.lam, "reducible values")
+    assert_close(out.V.cpu().numpy()[:, ks], ref.vec, "reducible vectors")
+    assert not bool(out.V.isnan().any())
+    srt = np.argsort(-red.d, kind="stable")          # presented in order: the deflated rows stay the caller's
+    out2 = _solve(W.Problem(red.kind, n, red.d[srt], red.z[srt], red.scalar))
+    assert np.array_equal(out2.lam.cpu().numpy(), out.lam.cpu().numpy())
+    grd = W.graded_arrow(n, rng, clusters=40)
+    out = _solve(grd)
+    flagged = np.nonzero(out.info.cpu().numpy() & 6)[0]
+    assert flagged.size > 20
+    ks = np.unique(np.concatenate([ks, flagged[:: max(1, flagged.size // 40)]]))
+    ref = oracle.arrow_eig(grd.d, grd.z, grd.scalar, ks=ks)
+    assert_close(out.lam.cpu().numpy()[ks], ref.lam, "graded values")
+    assert_close(out.V.cpu().numpy()[:, ks], ref.vec, "graded vectors")
+
+
+def test_larger_than_the_staged_poles(oracle_lib):
+    rng = np.random.default_rng(9)
+    pr = W.uniform_arrow(20500, rng, -1e4, 1e4)
+    out = _solve(pr, vectors=False)
+    _sampled(pr, out, vectors=False, count=4)
