@@ -12,7 +12,7 @@
 //               re-measure), norm, then its eigenvector, streamed to HBM
 //               (eq. eigenvecAi, Algorithm 4; complex for a Hermitian arrowhead, Sec. 6.1).
 //               Above FIN_MAX k_check, k_repair and k_vec take its place
-//   k_defl      arrowheads only: the eigenpairs a reducible one deflated (Sec. 1)
+//   k_defl      arrowheads above FIN_MAX: the eigenpairs a reducible one deflated (Sec. 1)
 // k_root gives G lanes of a wavefront to each eigenvalue (G = 64: one
 // wavefront per eigenvalue); the vectors are bound by the n^2 FP64 stores.
 
@@ -370,8 +370,13 @@ struct FinStage {
   double pv[FIN_COLS], sf[FIN_COLS], mu[FIN_COLS], inrm[FIN_COLS], sig[FIN_COLS];
   int col[FIN_COLS];     // output column, -1: none (past a deflated problem's order, or a redo block's)
   int redo[BLOCK];       // eigenvalues this block re-solves
-  int redo_count;
+  int redo_count, above;
 };
+
+// Relative distance (to the pole's and mu's size) within which a first-pass
+// eigenvalue that still needs a repair may lie on the other side of a deflated one:
+// such values are good to about K_nu eps, or eps of the pole near the origin.
+constexpr double DEFL_NEAR = 1e-6;
 
 template <int KIND, int W, int RPT>
 __device__ inline void finish_rows(const ProbDesc& D, int rt, int nc, const FinStage& L) {
@@ -481,7 +486,8 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
   }
   __syncthreads();
   const int count = redo ? L.redo_count : (D.V ? mine : 0);
-  if (redo && count > 0) stage_hot(D, lds);
+  bool staged = redo && count > 0;
+  if (staged) stage_hot(D, lds);
   for (int q0 = 0; q0 < count; q0 += FIN_COLS) {
     const int nc = min(FIN_COLS, count - q0);
     if (redo) {
@@ -494,6 +500,49 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
     }
     for (int rt = 0; rt * BLOCK * RPT < D.n; ++rt) finish_rows<KIND, W, RPT>(D, rt, nc, L);
     if (redo) __syncthreads();
+  }
+  if constexpr (KIND == KIND_ARROW) {
+    // The deflated eigenpairs, in turn.  One's column counts the eigenvalues at or
+    // above it: those of the first pass, which are final where no repair is due and
+    // tell the order elsewhere too unless they are within DEFL_NEAR of it; these few
+    // are re-solved here as well (the same values as their own block's).
+    const int nd = redo ? deflated_count(w) : 0;
+    const int np = reduced_m(w) + 1;
+    for (int s = (int)blockIdx.x; s < nd; s += redo_blocks) {
+      const double v = w.dv[s];
+      if (t == 0) L.above = 0;
+      for (int base = 0; base < np; base += BLOCK) {
+        if (t == 0) L.redo_count = 0;
+        __syncthreads();
+        const int k = base + t;
+        if (k < np) {
+          const double lam = dd_to_d(dd_add_d(dd_add_d(pval_dd<SK>(w.pv1[k]), 0.0), w.mu1[k]));
+          const bool near = fabs(lam - v) <= DEFL_NEAR * (fabs(w.pv1[k]) + fabs(w.mu1[k]));
+          if (near && check_body<SK, 1, false, DEFER_BLOCK>(D, opt, k, 0, nullptr, nullptr, false))
+            L.redo[atomicAdd(&L.redo_count, 1)] = k;
+          else if (lam >= v) atomicAdd(&L.above, 1);
+        }
+        __syncthreads();
+        const int again = L.redo_count;
+        if (again > 0 && !staged) {
+          stage_hot(D, lds);
+          staged = true;
+        }
+        for (int q = 0; q < again; ++q) {
+          check_body<SK, BLOCK, true>(D, opt, L.redo[q], t, lds, lds + sorted_count(D));
+          if (t == 0 && w.lr[L.redo[q]] >= v) L.above += 1;   // thread 0 wrote it
+        }
+        __syncthreads();
+      }
+      const int col = s + L.above;
+      if (t == 0) place_deflated_at(D, w, s, col);
+      if (D.V) {
+        double* vc = D.V + (size_t)col * (size_t)D.ldv;
+        for (int r = t; r < D.n; r += BLOCK)
+          __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -809,7 +858,7 @@ __global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, B
 }
 
 // The deflated eigenpairs of a reducible arrowhead: placed among the solved ones,
-// whose values are final after k_finish, and their vectors.  A block each, in
+// whose values are final, and their vectors (n > FIN_MAX).  A block each, in
 // turn; for the usual irreducible input every block returns at once.
 __global__ __launch_bounds__(BLOCK) void k_defl(ProbDesc D) {
   __shared__ int col;
@@ -996,7 +1045,7 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
       }
     }
   }
-  if (KIND == KIND_ARROW && D.n > 1)
+  if (KIND == KIND_ARROW && D.n > FIN_MAX)
     hipLaunchKernelGGL(k_defl, dim3((unsigned)std::min<int64_t>(D.n - 1, h->cus)), dim3(BLOCK), 0, st, D);
   if (tm) {
     h->ev_set = es;

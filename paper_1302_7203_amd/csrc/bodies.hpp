@@ -374,10 +374,8 @@ __host__ __device__ inline double deflated_entry(const Ws& w, int s, int j, doub
 // computed) with the deflated ones (descending); on a tie the reduced one
 // comes first.  Reduced eigenvalue k goes to column k + #{deflated > lambda_k},
 // deflated item s to column s + #{reduced >= delta_s} (which place_deflated returns).
-__host__ __device__ inline int place_deflated(const ProbDesc& D, const Ws& w, int s) {
-  const int np = reduced_m(w) + 1;
+__host__ __device__ inline void place_deflated_at(const ProbDesc& D, const Ws& w, int s, int col) {
   const double v = w.dv[s];
-  const int col = s + count_above(w.lr, np, v, true);
   D.lam[col] = v;
   if (D.shift) D.shift[col] = v;
   if (D.mu) D.mu[col] = 0.0;
@@ -385,6 +383,11 @@ __host__ __device__ inline int place_deflated(const ProbDesc& D, const Ws& w, in
   w.pv[col] = v; w.sf[col] = 0.0; w.mu[col] = 0.0; w.inrm[col] = 0.0;
   w.kbc[col] = NAN; w.knu[col] = NAN;
   w.cm[col] = s;
+}
+
+__host__ __device__ inline int place_deflated(const ProbDesc& D, const Ws& w, int s) {
+  const int col = s + count_above(w.lr, reduced_m(w) + 1, w.dv[s], true);
+  place_deflated_at(D, w, s, col);
   return col;
 }
 

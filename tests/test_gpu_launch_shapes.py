@@ -155,3 +155,26 @@ def test_larger_than_the_staged_poles(oracle_lib):
     pr = W.uniform_arrow(20500, rng, -1e4, 1e4)
     out = _solve(pr, vectors=False)
     _sampled(pr, out, vectors=False, count=4)
+
+
+def test_deflated_beside_repaired_eigenvalues(oracle_lib):
+    """Deflated values next to eigenvalues that a repair moves: a zero pole with a zero
+    shaft entry beside an eigenvalue far below the first pass's resolution (either sign),
+    and unit vectors inside tight clusters."""
+    for alpha in (1e-30, -1e-30, 1e-12):
+        d = np.array([1.0, 0.0, -1.0, 0.5, 0.5, -0.25])
+        z = np.array([1.0, 0.0, 1.0, 0.0, 0.0, 0.0])
+        pr = W.Problem(W.KIND_ARROW, 7, d, z, alpha)
+        out = _solve(pr)
+        ref = oracle.arrow_eig(d, z, alpha)
+        assert_close(out.lam.cpu().numpy(), ref.lam, f"alpha {alpha} values")
+        assert_close(out.V.cpu().numpy(), ref.vec, f"alpha {alpha} vectors")
+        assert np.array_equal((out.info.cpu().numpy() & 1024) != 0, ref.tau == 0)
+    rng = np.random.default_rng(31)
+    pr = W.graded_arrow(700, rng, clusters=60)
+    pr.z[rng.choice(699, 150, replace=False)] = 0.0
+    out = _solve(pr)
+    ref = oracle.arrow_eig(pr.d, pr.z, pr.scalar)
+    assert_close(out.lam.cpu().numpy(), ref.lam, "clusters: values")
+    assert_close(out.V.cpu().numpy(), ref.vec, "clusters: vectors")
+    assert np.array_equal((out.info.cpu().numpy() & 1024) != 0, ref.tau == 0)
