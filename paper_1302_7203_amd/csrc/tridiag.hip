@@ -48,6 +48,7 @@ struct Node {
 struct MergeDev {
   int lo, mid, hi;
   int nk;            // entries kept for the DPR1 solve (the others are deflated)
+  int nl;            // ... of them rows of the left block
   int big;           // its product goes to rocBLAS (else to k_td_update)
   int64_t out;       // offset of the merge's eigenvalues in the output pool; Qh follows (s x nk, ld s)
   int64_t dout;      // offset of the DPR1 solve's eigenvalues in its pool; its vectors follow (ld nk)
@@ -126,18 +127,24 @@ __global__ __launch_bounds__(TD_BLOCK) void k_td_expand(const MergeDev* mg, cons
   const double* dq = dl + nk;              // their vectors over the kept rows (ld nk)
   double* lo_out = out + m.out;
   double* qh = lo_out + s;
-  for (int c = (int)(blockIdx.x * TD_BLOCK + threadIdx.x); c < s; c += (int)gridDim.x * TD_BLOCK) {
+  // a wavefront per column: every lane finds the place, the lanes share the rows (a
+  // thread per column wrote its rows one after the other: 85 us at s = 1000)
+  const int lane = threadIdx.x & 63;
+  const int waves = (int)gridDim.x * (TD_BLOCK / 64);
+  for (int c = (int)blockIdx.x * (TD_BLOCK / 64) + (int)(threadIdx.x >> 6); c < s; c += waves) {
     if (c < nk) {
       const double v = dl[c];
       int lo = 0, hi = nf;                 // deflated values > v
       while (lo < hi) { const int md = (lo + hi) >> 1; if (lam[m.lo + defl[md]] > v) lo = md + 1; else hi = md; }
-      lo_out[c + lo] = v;
-      pos[m.lo + c] = c + lo;
-      info[m.lo + c + lo] = dinfo[m.lo + c];
-      double* col = qh + (size_t)c * s;
-      for (int r = 0; r < s; ++r) col[r] = 0.0;
-      for (int r = 0; r < nk; ++r) col[kept[r]] = dq[(size_t)c * nk + r];
-    } else {
+      if (lane == 0) {
+        lo_out[c + lo] = v;
+        pos[m.lo + c] = c + lo;
+        info[m.lo + c + lo] = dinfo[m.lo + c];
+      }
+      double* col = qh + (size_t)c * s;    // the kept rows and the others are disjoint
+      for (int r = lane; r < nf; r += 64) col[defl[r]] = 0.0;
+      for (int r = lane; r < nk; r += 64) col[kept[r]] = dq[(size_t)c * nk + r];
+    } else if (lane == 0) {
       const int f = c - nk;
       const double v = lam[m.lo + defl[f]];
       int lo = 0, hi = nk;                 // solved values >= v
@@ -164,10 +171,26 @@ __global__ __launch_bounds__(TD_BLOCK) void k_td_update(const MergeDev* mg, cons
     if (j < nk && m.big) continue;
     double v = 0.0;
     if (j < nk) {
-      const bool top = i < sl;
-      for (int r = 0; r < nk; ++r) {
+      // the kept rows ascend: the left block's are the first nl; four terms' loads ahead
+      // of the sum, which runs over them in order
+      const int r1 = i < sl ? m.nl : nk;
+      int r = i < sl ? 0 : m.nl;
+      const double* qr = Qold + (size_t)m.lo * n + (m.lo + i);
+      const double* hc = qh + (size_t)j * s;
+      for (; r + 4 <= r1; r += 4) {
+        double a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int kr = kept[r + u];
+          a[u] = qr[(size_t)kr * n];
+          b[u] = hc[kr];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v = fma(a[u], b[u], v);
+      }
+      for (; r < r1; ++r) {
         const int kr = kept[r];
-        if ((kr < sl) == top) v = fma(Qold[(size_t)(m.lo + kr) * n + (m.lo + i)], qh[(size_t)j * s + kr], v);
+        v = fma(qr[(size_t)kr * n], hc[kr], v);
       }
     } else {
       const int d = kept[j];                                    // deflated row (map continues past nk)
@@ -333,7 +356,7 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     // the merges of this level; u of every one, then eigenvalues and u to the host
     all.clear();
     for (const Node& p : nodes)
-      if (p.height == lev && p.left >= 0) all.push_back(MergeDev{p.lo, p.mid, p.hi, 0, 0, 0, 0, 0});
+      if (p.height == lev && p.left >= 0) all.push_back(MergeDev{p.lo, p.mid, p.hi, 0, 0, 0, 0, 0, 0});
     MergeDev* drec = (MergeDev*)recs.p;
     int64_t widest = 1;   // the largest merge of the level sizes the grids (they stride over the rest)
     for (const MergeDev& m : all) widest = std::max<int64_t>(widest, m.hi - m.lo);
@@ -361,12 +384,13 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
         umax = std::max(umax, fabs(hl[(size_t)n + t]));
       }
       const double tol = 8.0 * eps * std::max(dmax, umax * 0.7071067811865476);
-      int nk = 0;
+      int nk = 0, nl = 0;
       idx.clear();
       for (int t = 0; t < s; ++t) {
         const double ut = hl[(size_t)n + p.lo + t];
         if (p.beta != 0.0 && 1.4142135623730951 * fabs(p.beta) * fabs(ut) > tol) {
           hmap[(size_t)p.lo + nk] = t;
+          if (t < p.mid - p.lo) nl = nk + 1;
           hc[(size_t)p.lo + nk] = hl[(size_t)p.lo + t];
           hc[(size_t)n + p.lo + nk] = ut;
           ++nk;
@@ -377,6 +401,7 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
       std::stable_sort(idx.begin(), idx.end(), [&](int x, int y) { return hl[(size_t)p.lo + x] > hl[(size_t)p.lo + y]; });
       for (size_t f = 0; f < idx.size(); ++f) hmap[(size_t)p.lo + nk + f] = idx[f];
       m.nk = nk;
+      m.nl = nl;
       m.out = off;
       m.dout = doff;
       // products of more than 2^22 multiply-adds go to rocBLAS
@@ -423,7 +448,7 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
       if (rc != ARROW_OK) return rc;
       if (rc2 != ARROW_OK) return rc2;
     }
-    hipLaunchKernelGGL(k_td_expand, dim3(grid_x(widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
+    hipLaunchKernelGGL(k_td_expand, dim3(grid_x(widest * 64), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
                        (const int*)mapb.p, lam, (const double*)dpool.p, (const uint32_t*)infod.p, (double*)outp.p,
                        (uint32_t*)infop.p, (int*)posb.p);
     hipLaunchKernelGGL(k_td_put_lam, dim3(grid_x(widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
@@ -448,7 +473,8 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     hipLaunchKernelGGL(k_td_update, dim3(grid_x(widest * widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
                        (const int*)mapb.p, (const int*)posb.p, (const double*)outp.p, (int)n, (const double*)qb[in],
                        qb[outb]);
-    hipLaunchKernelGGL(k_td_scatter, dim3(grid_x(widest * widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
+    if (coff > 0)
+      hipLaunchKernelGGL(k_td_scatter, dim3(grid_x(widest * widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
                        (const int*)posb.p, (const double*)scratch, (int)n, qb[outb]);
     // the host arrays copied to the device above are refilled next level: the plan's
     // destruction synchronised the stream after those copies; without a plan, wait here
