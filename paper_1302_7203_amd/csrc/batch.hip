@@ -459,6 +459,7 @@ struct arrow_batch_s {
   std::vector<int32_t> tabs;   // item_start (count+1), lanes (count), vec_start (count+1), vec_mode (count),
                                // check_start (count+1), vec_prob (one per vector tile), check_prob (one per
                                // check-stage item)
+  std::vector<char> image;     // both as they are copied to the device
   BatchArgs args;
   int persistent_blocks, check_blocks, remedy_blocks, repair_blocks;
   hipGraph_t graph;
@@ -660,10 +661,11 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   b->repair_per = (int)std::max<int64_t>(1, 1024 / count);
   b->total_vec = (int32_t)vchunks;
   hipStream_t st = h->stream;
-  if (hipMemcpyAsync(base + L.off_desc, b->descs.data(), (size_t)count * sizeof(ProbDesc), hipMemcpyHostToDevice,
-                     st) != hipSuccess ||
-      hipMemcpyAsync(base + L.off_tab, b->tabs.data(), b->tabs.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                     st) != hipSuccess) {
+  // descriptors and tables, neighbours in the device block, in one copy
+  b->image.resize(L.off_redo - L.off_desc);
+  memcpy(b->image.data(), b->descs.data(), (size_t)count * sizeof(ProbDesc));
+  memcpy(b->image.data() + (L.off_tab - L.off_desc), b->tabs.data(), b->tabs.size() * sizeof(int32_t));
+  if (hipMemcpyAsync(base + L.off_desc, b->image.data(), b->image.size(), hipMemcpyHostToDevice, st) != hipSuccess) {
     if (b->own_dev) (void)hipFree(b->dev);
     delete b;
     return ARROW_ERR_HIP;

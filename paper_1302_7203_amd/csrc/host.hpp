@@ -36,6 +36,10 @@ struct arrow_handle_s {
   void* blas;         // rocBLAS handle of tridiag_eig's GEMMs, made on first use
   void* td_ws;        // tridiag_eig's device buffers (grown on demand, kept)
   size_t td_cap;      // bytes
+  void* td_plan;      // its merge plans' device block (grown on demand, kept)
+  size_t td_plan_cap; // bytes
+  void* td_host;      // its pinned staging (grown on demand, kept)
+  size_t td_host_cap; // bytes
   uint32_t magic;
 };
 

@@ -223,15 +223,26 @@ unsigned grid_x(int64_t items) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, 64));
 }
 
-struct DevBuf {
-  void* p = nullptr;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
+// a buffer the handle keeps, grown to `bytes` (the stream drained first, as the old
+// one may be in use)
+int grow(void** p, size_t* cap, size_t bytes, bool host, hipStream_t st) {
+  if (bytes <= *cap) return ARROW_OK;
+  if (*p) {
+    (void)hipStreamSynchronize(st);
+    (void)(host ? hipHostFree(*p) : hipFree(*p));
+    *p = nullptr;
+    *cap = 0;
   }
-  int alloc(size_t bytes) {
-    return hipMalloc(&p, bytes) == hipSuccess ? ARROW_OK : ARROW_ERR_NOMEM;
+  if ((host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes)) != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+    return ARROW_ERR_NOMEM;
   }
-};
+  *cap = bytes;
+  return ARROW_OK;
+}
+
+size_t up256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
 }  // namespace
 
@@ -244,6 +255,16 @@ void tridiag_release(arrow_handle_t h) {
     (void)hipFree(h->td_ws);
     h->td_ws = nullptr;
     h->td_cap = 0;
+  }
+  if (h->td_plan) {
+    (void)hipFree(h->td_plan);
+    h->td_plan = nullptr;
+    h->td_plan_cap = 0;
+  }
+  if (h->td_host) {
+    (void)hipHostFree(h->td_host);
+    h->td_host = nullptr;
+    h->td_host_cap = 0;
   }
 }
 
@@ -261,11 +282,29 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
   DeviceGuard g(h->device);
   hipStream_t st = h->stream;
   (void)hipGetLastError();
+  // Pinned staging, so that copies neither wait for the runtime's own nor for each
+  // other: what comes from the device (b, then each level's eigenvalues and u), the
+  // level's merge records, and what goes back once its deflation is decided -- kept
+  // entries, row map and records, contiguous as on the device, one copy.
+  const size_t cpool_bytes = up256(2 * (size_t)n * sizeof(double)), map_bytes = up256((size_t)n * sizeof(int)),
+               rec_bytes = up256((size_t)n * sizeof(MergeDev) + 16), back_bytes = 2 * (size_t)n * sizeof(double);
+  int rc = grow(&h->td_host, &h->td_host_cap, up256(back_bytes) + rec_bytes + cpool_bytes + map_bytes + rec_bytes, true,
+                st);
+  if (rc) return rc;
+  char* pin = (char*)h->td_host;
+  double* hl = (double*)pin;                                  // eigenvalues, then u
+  char* rec0 = pin + up256(back_bytes);                       // records before deflation, and copy spans
+  char* level = rec0 + rec_bytes;                             // the level's upload
+  double* hc = (double*)level;
+  int* hmap = (int*)(level + cpool_bytes);
+  char* rec1 = level + cpool_bytes + map_bytes;
+  const size_t level_bytes = cpool_bytes + map_bytes + rec_bytes;
   std::vector<double> hb((size_t)std::max<int64_t>(1, n - 1), 0.0);
   if (n > 1) {
-    if (hipMemcpyAsync(hb.data(), b, (size_t)(n - 1) * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (hipMemcpyAsync(hl, b, (size_t)(n - 1) * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return ARROW_ERR_HIP;
+    memcpy(hb.data(), hl, (size_t)(n - 1) * sizeof(double));
     for (int64_t i = 0; i + 1 < n; ++i)
       if (!(hb[(size_t)i] - hb[(size_t)i] == 0.0)) return -4;   // the tree needs finite off-diagonals
   }
@@ -284,23 +323,15 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     size_t bytes;
   };
   void *p_lamu, *p_cpool, *p_qbuf, *p_outp, *p_dpool, *p_infop, *p_infod, *p_map, *p_pos, *p_recs;
-  const Part parts[] = {{&p_lamu, 2 * (size_t)n * sizeof(double)},  {&p_cpool, 2 * (size_t)n * sizeof(double)},
-                        {&p_qbuf, 2 * nn * sizeof(double)},          {&p_outp, ((size_t)n + nn) * sizeof(double)},
-                        {&p_dpool, ((size_t)n + nn) * sizeof(double)}, {&p_infop, (size_t)n * sizeof(uint32_t)},
-                        {&p_infod, (size_t)n * sizeof(uint32_t)},    {&p_map, (size_t)n * sizeof(int)},
-                        {&p_pos, (size_t)n * sizeof(int)},           {&p_recs, (size_t)n * sizeof(MergeDev) + 16}};
+  const Part parts[] = {{&p_lamu, 2 * (size_t)n * sizeof(double)},  {&p_qbuf, 2 * nn * sizeof(double)},
+                        {&p_outp, ((size_t)n + nn) * sizeof(double)}, {&p_dpool, ((size_t)n + nn) * sizeof(double)},
+                        {&p_infop, (size_t)n * sizeof(uint32_t)},    {&p_infod, (size_t)n * sizeof(uint32_t)},
+                        {&p_pos, (size_t)n * sizeof(int)},           {&p_cpool, cpool_bytes},
+                        {&p_map, map_bytes},                         {&p_recs, rec_bytes}};
   size_t total = 0;
   for (const Part& q : parts) total += (q.bytes + 255) / 256 * 256;
-  if (total > h->td_cap) {
-    if (h->td_ws) (void)hipFree(h->td_ws);
-    h->td_ws = nullptr;
-    h->td_cap = 0;
-    if (hipMalloc(&h->td_ws, total) != hipSuccess) {
-      h->td_ws = nullptr;
-      return ARROW_ERR_NOMEM;
-    }
-    h->td_cap = total;
-  }
+  rc = grow(&h->td_ws, &h->td_cap, total, false, st);
+  if (rc) return rc;
   {
     char* at = (char*)h->td_ws;
     for (const Part& q : parts) {
@@ -312,9 +343,6 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     void* p;
   } lamu{p_lamu}, cpool{p_cpool}, qbuf{p_qbuf}, outp{p_outp}, dpool{p_dpool}, infop{p_infop}, infod{p_infod},
       mapb{p_map}, posb{p_pos}, recs{p_recs};
-  DevBuf bws;
-  size_t bws_bytes = 0;
-  int rc;
   double* lam = (double*)lamu.p;
   double* u = lam + n;
   double* qb[2] = {(double*)qbuf.p, (double*)qbuf.p + nn};
@@ -333,8 +361,8 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
   std::vector<MergeDev> all;
   std::vector<int2> copies;
   std::vector<arrow_desc_t> descs;
-  std::vector<double> hl((size_t)2 * n), hc((size_t)2 * n, 0.0);
-  std::vector<int> hmap((size_t)n), idx;
+  std::vector<int> idx;
+  memset(hc, 0, cpool_bytes);
   for (int lev = 1; lev <= H; ++lev) {
     const int in = (lev - 1) & 1, outb = lev & 1;
     // nodes of height lev-2 under a parent of height lev: to the input buffer first
@@ -345,11 +373,13 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
         if (nodes[(size_t)c].height == lev - 2) copies.push_back(make_int2(nodes[(size_t)c].lo, nodes[(size_t)c].hi));
     }
     if (!copies.empty()) {
-      int2* dsp = (int2*)recs.p;
-      if (hipMemcpyAsync(dsp, copies.data(), copies.size() * sizeof(int2), hipMemcpyHostToDevice, st) != hipSuccess)
+      // at the records' end of the device pool's map, free until the level's upload; its
+      // staging shares the records' (at most n/2 spans, then at most n/2 records)
+      int2* dsp = (int2*)mapb.p;
+      int2* hsp = (int2*)(rec0 + rec_bytes) - copies.size();
+      memcpy(hsp, copies.data(), copies.size() * sizeof(int2));
+      if (hipMemcpyAsync(dsp, hsp, copies.size() * sizeof(int2), hipMemcpyHostToDevice, st) != hipSuccess)
         return ARROW_ERR_HIP;
-      // recs is written again below, after this kernel in stream order; the host's copy
-      // list is refilled only after the next synchronisation
       hipLaunchKernelGGL(k_td_copy, dim3(64, (unsigned)copies.size()), dim3(TD_BLOCK), 0, st, dsp, (int)n,
                          qb[in ^ 1], qb[in]);
     }
@@ -360,11 +390,12 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     MergeDev* drec = (MergeDev*)recs.p;
     int64_t widest = 1;   // the largest merge of the level sizes the grids (they stride over the rest)
     for (const MergeDev& m : all) widest = std::max<int64_t>(widest, m.hi - m.lo);
-    if (hipMemcpyAsync(drec, all.data(), all.size() * sizeof(MergeDev), hipMemcpyHostToDevice, st) != hipSuccess)
+    memcpy(rec0, all.data(), all.size() * sizeof(MergeDev));
+    if (hipMemcpyAsync(drec, rec0, all.size() * sizeof(MergeDev), hipMemcpyHostToDevice, st) != hipSuccess)
       return ARROW_ERR_HIP;
     hipLaunchKernelGGL(k_td_gather_u, dim3(grid_x(widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec, (int)n,
                        qb[in], u);
-    if (hipMemcpyAsync(hl.data(), lam, 2 * (size_t)n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (hipMemcpyAsync(hl, lam, 2 * (size_t)n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return ARROW_ERR_HIP;
     // Deflation (the usual one of divide and conquer): entry j is dropped when
@@ -424,24 +455,15 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
         doff += (int64_t)nk + (int64_t)nk * nk;
       }
     }
-    if (hipMemcpyAsync(drec, all.data(), all.size() * sizeof(MergeDev), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(mapb.p, hmap.data(), (size_t)n * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(cpool.p, hc.data(), 2 * (size_t)n * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess)
-      return ARROW_ERR_HIP;
+    memcpy(rec1, all.data(), all.size() * sizeof(MergeDev));
+    if (hipMemcpyAsync(cpool.p, level, level_bytes, hipMemcpyHostToDevice, st) != hipSuccess) return ARROW_ERR_HIP;
     if (!descs.empty()) {
-      // the plan's device block comes from one buffer, grown when a level needs more
+      // the plan's device block comes from one buffer that the handle keeps
       const size_t need = arrow_batch_workspace_size((int64_t)descs.size(), descs.data());
-      if (need > bws_bytes) {
-        (void)hipStreamSynchronize(st);
-        if (bws.p) (void)hipFree(bws.p);
-        bws.p = nullptr;
-        bws_bytes = 0;
-        if ((rc = bws.alloc(need))) return rc;
-        bws_bytes = need;
-      }
+      if ((rc = grow(&h->td_plan, &h->td_plan_cap, need, false, st))) return rc;
       arrow_batch_t plan = nullptr;
       rc = arrow_batch_create(h, (int64_t)descs.size(), descs.data(), (double*)cpool.p, (double*)dpool.p,
-                              (uint32_t*)infod.p, bws.p, bws_bytes, 0, &plan);
+                              (uint32_t*)infod.p, h->td_plan, h->td_plan_cap, 0, &plan);
       if (rc != ARROW_OK) return rc > 0 ? rc : ARROW_ERR_STATE;
       rc = arrow_batch_run(plan);
       const int rc2 = arrow_batch_destroy(plan);   // synchronises the stream: the host arrays may be reused
