@@ -56,9 +56,10 @@ struct BatchArgs {
   const int32_t* vec_prob;   // per vector tile: its problem
   const int32_t* check_prob; // per check-stage item: its problem
   uint2* redo;               // (problem, eigenvalue) pairs left for k_b_remedy
-  uint32_t* counters;        // [0] first-pass queue, [1] length of redo
+  uint32_t* counters;        // [0] shared root items taken, [1] length of redo, [2] other root items taken
   int32_t count;
   int32_t total_items;
+  int32_t shared_items;      // root items of orders whose arrays one wavefront's LDS does not hold
   int32_t total_check;
   int32_t chunk;             // root items taken at a time
 };
@@ -73,7 +74,7 @@ __device__ inline int find_problem(const int32_t* start, int count, int x) {
 }
 
 __global__ __launch_bounds__(BLOCK) void k_b_prep(BatchArgs B) {
-  if (blockIdx.x == 0 && threadIdx.x < 2) B.counters[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 3) B.counters[threadIdx.x] = 0;
   const ProbDesc D = B.descs[blockIdx.x];
   if (sorted_count(D) > 0) {
     switch (D.kind) {
@@ -212,48 +213,104 @@ constexpr int CHUNK_FROM = 8;
 #define AHD_ROOT_WAVES 4
 #endif
 constexpr int ROOT_WAVES = AHD_ROOT_WAVES;
+//
+// Items [0, B.shared_items), the orders above 640 that a wavefront's own slice holds
+// in part or not at all: a block takes four consecutive items, a wavefront each, and
+// stages the first one's problem in the LDS of all four slices (both arrays up to
+// n = 2561, the poles alone up to 5121; a wavefront whose item is already the next
+// problem's reads through the cache).  The other items: a wavefront each, from its
+// own slice, without waiting for the block.  From the caches a wavefront waits for
+// most of its loads where there are few beside it, and the arrays of many problems
+// outgrow the L2.  Whole plans, own slices alone against this: 32 problems
+// n = 48..2048 300 -> 241 us, 400 of n = 16..2048 1395 -> 1193, 365 of 768..1536
+// 3061 -> 2707, 179 of 1536..3072 6353 -> 4925.
 __global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(ROOT_WAVES))) void k_b_root(
     BatchArgs B, Options opt) {
+  constexpr int WAVES = STAGE_BLOCK / WAVE;
   const int lane = threadIdx.x & (WAVE - 1);
-  __shared__ double lds_all[STAGE_BLOCK / WAVE][ROOT_STAGE > 0 ? ROOT_STAGE : 1];
-  double* lds = lds_all[threadIdx.x / WAVE];
-  int staged = -1;   // the problem whose arrays the slice holds
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  __shared__ double lds_all[WAVES][ROOT_STAGE > 0 ? ROOT_STAGE : 1];
+  __shared__ int taken;
+  // the shared items, then (whole = false) the wavefronts' own: one loop, one copy of the bodies
+  double* own = lds_all[wave];
+  int staged = -1;   // the problem whose arrays the LDS (or, later, the slice) holds
+  bool whole = B.shared_items > 0;
+  int item = 0, last = 0;
   for (;;) {
-    int first = 0;
-    if (lane == 0) first = (int)atomicAdd(&B.counters[0], (unsigned)B.chunk);
-    first = __builtin_amdgcn_readfirstlane(first);   // the items, their problem and its record are the wavefront's
-    if (first >= B.total_items) break;
-    const int last = min(first + B.chunk, B.total_items);
-    for (int item = first; item < last; ++item) {
+    int p0 = -1, hot = 0;
+    if (whole) {
+      __syncthreads();   // the arrays and `taken` of the turn before are done with
+      if (threadIdx.x == 0) taken = (int)atomicAdd(&B.counters[0], (unsigned)WAVES);
+      __syncthreads();
+      const int first = __builtin_amdgcn_readfirstlane(taken);
+      if (first < B.shared_items) {
+        p0 = find_problem(B.item_start, B.count, first);
+        const ProbDesc& D0 = B.descs[p0];
+        const int ns0 = sorted_count(D0);
+        hot = B.lanes[p0] > 16 ? 0 : (2 * ns0 <= WAVES * ROOT_STAGE ? 1 : (ns0 <= WAVES * ROOT_STAGE ? 2 : 0));
+        if (hot && staged != p0) {
+          const Ws w = ws_view(D0.ws, D0.n);
+          double* all = lds_all[0];
+          for (int j = threadIdx.x; j < ns0; j += STAGE_BLOCK) {
+            all[j] = w.ds[j];
+            if (hot == 1) all[ns0 + j] = w.ch[j];
+          }
+          staged = p0;
+          __syncthreads();
+        }
+        item = first + wave;
+      } else {
+        whole = false;
+        staged = -1;
+        item = last = 0;
+        __syncthreads();   // nobody reads the shared arrays any more
+      }
+    }
+    if (!whole && item >= last) {
+      int first = 0;
+      if (lane == 0) first = B.shared_items + (int)atomicAdd(&B.counters[2], (unsigned)B.chunk);
+      item = __builtin_amdgcn_readfirstlane(first);   // the items, their problem and its record are the wavefront's
+      if (item >= B.total_items) break;
+      last = min(item + B.chunk, B.total_items);
+    }
+    if (!whole || item < B.shared_items) {
       const int p = find_problem(B.item_start, B.count, item);
       const ProbDesc D = B.descs[p];
       const int G = B.lanes[p];
       const int k = (item - B.item_start[p]) * (WAVE / G) + lane / G;
       const int ns = sorted_count(D);
-      const int hot = G > 16 ? 0 : (2 * ns <= ROOT_STAGE ? 1 : (ns <= ROOT_STAGE ? 2 : 0));
-      if (hot && staged != p) {
-        // the slice is the wavefront's own: its LDS reads and writes run in
-        // order, so only the compiler must not move them across the copy
-        const Ws w = ws_view(D.ws, D.n);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int j = lane; j < ns; j += WAVE) {
-          lds[j] = w.ds[j];
-          if (hot == 1) lds[ns + j] = w.ch[j];
+      const double* at = lds_all[0];
+      if (whole) {
+        if (p != p0) hot = 0;
+      } else {
+        at = own;
+        hot = G > 16 ? 0 : (2 * ns <= ROOT_STAGE ? 1 : (ns <= ROOT_STAGE ? 2 : 0));
+        if (hot && staged != p) {
+          // the slice is the wavefront's own: its LDS reads and writes run in
+          // order, so only the compiler must not move them across the copy
+          const Ws w = ws_view(D.ws, D.n);
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          for (int j = lane; j < ns; j += WAVE) {
+            own[j] = w.ds[j];
+            if (hot == 1) own[ns + j] = w.ch[j];
+          }
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          staged = p;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        staged = p;
       }
       const bool valid = k < D.n;
       switch (D.kind) {
         case KIND_ARROW:
-        case KIND_HERM: root_kind<KIND_ARROW>(D, opt, G, k, lane, valid, hot, lds); break;   // HERM: the real arrowhead on |z|
-        case KIND_DPR1: root_kind<KIND_DPR1>(D, opt, G, k, lane, valid, hot, lds); break;
-        default: root_kind<KIND_SVD>(D, opt, G, k, lane, valid, hot, lds); break;
+        case KIND_HERM: root_kind<KIND_ARROW>(D, opt, G, k, lane, valid, hot, at); break;   // HERM: the real arrowhead on |z|
+        case KIND_DPR1: root_kind<KIND_DPR1>(D, opt, G, k, lane, valid, hot, at); break;
+        default: root_kind<KIND_SVD>(D, opt, G, k, lane, valid, hot, at); break;
       }
     }
+    __builtin_amdgcn_wave_barrier();
+    ++item;
   }
 }
 
@@ -611,6 +668,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   char* base = (char*)b->dev;
   size_t wsoff = L.off_ws;
   int64_t items = 0, vchunks = 0, citems = 0;
+  int64_t shared = 0;   // orders decrease: the items up to the last problem larger than a wavefront's slice
   for (int64_t q = 0; q < count; ++q) {
     const arrow_desc_t& a = descs[order[(size_t)q]];
     ProbDesc D{};
@@ -633,6 +691,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
     lanes[q] = G;
     item_start[q] = (int32_t)items;
     items += (a.n + (WAVE / G) - 1) / (WAVE / G);
+    if (G <= 16 && 2 * (a.kind == ARROW_KIND_DPR1 ? a.n : a.n - 1) > ROOT_STAGE) shared = items;
     check_start[q] = (int32_t)citems;
     for (int64_t t = (a.n + WAVE - 1) / WAVE; t > 0; --t) check_prob[citems++] = (int32_t)q;
     vec_start[q] = (int32_t)vchunks;
@@ -684,6 +743,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   A.counters = (uint32_t*)base;
   A.count = (int32_t)count;
   A.total_items = b->total_items;
+  A.shared_items = (int32_t)shared;
   // persistent grid: enough resident wavefronts to fill every SIMD several times
   const int64_t want = (int64_t)h->cus * 4 * ROOT_WAVES * WAVE / STAGE_BLOCK;
   const int64_t need = ((int64_t)items * WAVE + STAGE_BLOCK - 1) / STAGE_BLOCK;
