@@ -363,6 +363,18 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
   std::vector<arrow_desc_t> descs;
   std::vector<int> idx;
   memset(hc, 0, cpool_bytes);
+  // The level's plan outlives its solve until the next level has waited for the
+  // eigenvalues: destroying it waits for the stream, and so the launches that follow
+  // the solve are queued while it runs, one wait a level instead of two.
+  struct Pending {
+    arrow_batch_t plan = nullptr;
+    int close() {
+      const int r = plan ? arrow_batch_destroy(plan) : ARROW_OK;
+      plan = nullptr;
+      return r;
+    }
+    ~Pending() { (void)close(); }
+  } pending;
   for (int lev = 1; lev <= H; ++lev) {
     const int in = (lev - 1) & 1, outb = lev & 1;
     // nodes of height lev-2 under a parent of height lev: to the input buffer first
@@ -398,6 +410,7 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     if (hipMemcpyAsync(hl, lam, 2 * (size_t)n * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return ARROW_ERR_HIP;
+    if ((rc = pending.close()) != ARROW_OK) return rc;
     // Deflation (the usual one of divide and conquer): entry j is dropped when
     // sqrt2 |beta| |u_j| <= 8 eps max(|d|_max, |u|_max / sqrt2) -- u has norm
     // sqrt2 -- a perturbation of T of that size; it leaves (d_j, e_j).  The
@@ -461,14 +474,10 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
       // the plan's device block comes from one buffer that the handle keeps
       const size_t need = arrow_batch_workspace_size((int64_t)descs.size(), descs.data());
       if ((rc = grow(&h->td_plan, &h->td_plan_cap, need, false, st))) return rc;
-      arrow_batch_t plan = nullptr;
       rc = arrow_batch_create(h, (int64_t)descs.size(), descs.data(), (double*)cpool.p, (double*)dpool.p,
-                              (uint32_t*)infod.p, h->td_plan, h->td_plan_cap, 0, &plan);
+                              (uint32_t*)infod.p, h->td_plan, h->td_plan_cap, 0, &pending.plan);
       if (rc != ARROW_OK) return rc > 0 ? rc : ARROW_ERR_STATE;
-      rc = arrow_batch_run(plan);
-      const int rc2 = arrow_batch_destroy(plan);   // synchronises the stream: the host arrays may be reused
-      if (rc != ARROW_OK) return rc;
-      if (rc2 != ARROW_OK) return rc2;
+      if ((rc = arrow_batch_run(pending.plan)) != ARROW_OK) return rc;
     }
     hipLaunchKernelGGL(k_td_expand, dim3(grid_x(widest * 64), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
                        (const int*)mapb.p, lam, (const double*)dpool.p, (const uint32_t*)infod.p, (double*)outp.p,
@@ -498,9 +507,8 @@ int tridiag_eig(arrow_handle_t h, int64_t n, const double* a, const double* b, d
     if (coff > 0)
       hipLaunchKernelGGL(k_td_scatter, dim3(grid_x(widest * widest), (unsigned)all.size()), dim3(TD_BLOCK), 0, st, drec,
                        (const int*)posb.p, (const double*)scratch, (int)n, qb[outb]);
-    // the host arrays copied to the device above are refilled next level: the plan's
-    // destruction synchronised the stream after those copies; without a plan, wait here
-    if (descs.empty() && hipStreamSynchronize(st) != hipSuccess) return ARROW_ERR_HIP;
+    // The staging needs no wait here: the next level writes `rec0` after this level's
+    // wait, which came behind the copy from it, and `level` after its own.
   }
   // results: eigenvalues (descending) and the root's block
   const int fin = H & 1;

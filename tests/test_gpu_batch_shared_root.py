@@ -20,7 +20,7 @@ PLANS = {
 MAKE = {"arrow": W.uniform_arrow, "dpr1": W.dpr1, "svd": W.svd_arrow, "herm": W.herm_arrow}
 
 
-@pytest.mark.parametrize("lanes", [0, 1, 32])
+@pytest.mark.parametrize("lanes", [0, 4, 32])
 @pytest.mark.parametrize("plan", PLANS)
 def test_shared_and_own_items(plan, lanes):
     import torch
@@ -31,14 +31,16 @@ def test_shared_and_own_items(plan, lanes):
     rng = np.random.default_rng(23)
     probs = [MAKE[kind](n, rng) for kind, n in PLANS[plan]]
     if lanes:
-        binding.set_option(binding.OPT_LANES, lanes)
+        batch.set_lanes_table([binding.INT32_MAX], [lanes], device=0)
     try:
         b = batch.Batch(probs, device=dev)
         for _ in range(2):
             b.out_pool.fill_(float("nan"))
             b.run()
     finally:
-        binding.set_option(binding.OPT_LANES, 0)
+        if lanes:
+            batch.set_lanes_table([], [], device=0)
+            binding.apply_tuned(binding.handle(0))
     torch.cuda.synchronize(dev)
     for q, pr in enumerate(probs):
         d = torch.from_numpy(pr.d).to(dev)
