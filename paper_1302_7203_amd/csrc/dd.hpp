@@ -76,18 +76,16 @@ __host__ __device__ inline dd dd_mul_d(dd a, double b) {
   return fast_two_sum(p.hi, p.lo);
 }
 
-// three quotient digits, then renormalise; r is 1/b.hi to about an ulp, and each
-// digit's error is in the next one's remainder
-__host__ __device__ inline dd dd_div_r(dd a, dd b, double r) {
-  const double q1 = a.hi * r;
-  dd rem = dd_sub(a, dd_mul_d(b, q1));
-  const double q2 = rem.hi * r;
-  rem = dd_sub(rem, dd_mul_d(b, q2));
-  const double q3 = rem.hi * r;
-  return dd_add_d(fast_two_sum(q1, q2), q3);
+// three quotient digits, then renormalise
+__host__ __device__ inline dd dd_div(dd a, dd b) {
+  double q1 = a.hi / b.hi;
+  dd r = dd_sub(a, dd_mul_d(b, q1));
+  double q2 = r.hi / b.hi;
+  r = dd_sub(r, dd_mul_d(b, q2));
+  double q3 = r.hi / b.hi;
+  dd q = fast_two_sum(q1, q2);
+  return dd_add_d(q, q3);
 }
-
-__host__ __device__ inline dd dd_div(dd a, dd b) { return dd_div_r(a, b, 1.0 / b.hi); }
 
 __host__ __device__ inline double dd_to_d(dd a) { return a.hi + a.lo; }
 

@@ -161,33 +161,6 @@ __host__ __device__ inline double recip(double x) {
 #endif
 }
 
-// a / b and sqrt(x) where one follows another in the chain of scalar steps that
-// every pass waits for: about half the instructions, and half the dependent ones,
-// of the correctly rounded sequences (which also rescale operands near the ends of
-// the exponent range), within an ulp.  v_div_fixup gives zeros, infinities and NaNs
-// their IEEE quotients.
-__host__ __device__ inline double fdiv(double a, double b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_div_fixup(a * recip3(b), b, a);
-#else
-  return a / b;
-#endif
-}
-
-__host__ __device__ inline double fsqrt(double x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;           // Goldschmidt: g -> sqrt(x), h -> 1 / (2 sqrt(x))
-  const double r = fma(-h, g, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
-  g = fma(fma(-g, g, x), h, g);
-  return (x > 0.0 && x < INFINITY) ? g : (x < 0.0 ? NAN : x);
-#else
-  return sqrt(x);
-#endif
-}
-
 // ---------------------------------------------------------------------------
 // group reductions.  Every step adds a value and its partner's, so every lane
 // of the group ends with the same bits.  Partners within 16 lanes come from
@@ -349,8 +322,8 @@ __host__ __device__ inline double pos_root(double beta, double s) {
   if (mx == INFINITY) return (beta == -INFINITY && s < INFINITY) ? 0.0 : INFINITY;
   const int k = ilogb(mx);
   const double b = ldexp(beta, -k), q = ldexp(s, -k);
-  const double r = fsqrt(fma(b, b, 4.0 * q * q));
-  return (b >= 0.0) ? ldexp(0.5 * (b + r), k) : (2.0 * s) * fdiv(q, r - b);
+  const double r = sqrt(fma(b, b, 4.0 * q * q));
+  return (b >= 0.0) ? ldexp(0.5 * (b + r), k) : (2.0 * s) * (q / (r - b));
 }
 
 // ---------------------------------------------------------------------------
@@ -499,7 +472,7 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
     // Algorithm 2: b = (-a + sum_{j<i} + sum_{j>i}) / zeta_i^2, all in FP64
     f1 = gsum<G>(f1);
     f2 = gsum<G>(f2);
-    r.b = fdiv((-a.hi + f1) + f2, ci);
+    r.b = ((-a.hi + f1) + f2) / ci;
     num_abs = fabs(r.b) * ci;
   } else {
     p1 = gsum_dd<G>(dd_norm(p1));
@@ -510,10 +483,10 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
     if (-a.hi > 0) { pp = dd_add(dd_neg(a), p1); qq = dd_neg(p2); }
     else { pp = p1; qq = dd_sub(a, p2); }
     const dd num = dd_sub(pp, qq);
-    r.b = dd_to_d(dd_div_r(num, dd{P.ch[i], P.cl[i]}, recip3(P.ch[i])));
+    r.b = dd_to_d(dd_div(num, dd{P.ch[i], P.cl[i]}));
     num_abs = fabs(num.hi);
   }
-  r.Kb = fdiv(fabs(a.hi) + fabs(f1) + fabs(f2), num_abs);
+  r.Kb = (fabs(a.hi) + fabs(f1) + fabs(f2)) / num_abs;
   // The bracket of the extreme eigenvalue on the requested side, in the
   // variable x = side*nu.  Lower end: the rightmost pole of A_i^{-1}'s Pick
   // function, y = side*delta_j of the pole next to d_i on that side (the
@@ -528,7 +501,7 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
   const int jn = i - side;
   const double xl = (jn >= 0 && jn < m) ? fmax(sg * recip(pdiff<KIND>(P.ds[jn], di)), 0.0) : 0.0;
   // the square root of the total residue (sum_j c_j / e_j^2 + 1) / zeta_i^2
-  const double srt = fdiv(fdiv(fsqrt(fma(gs, gs, r2)), gs), fsqrt(ci));
+  const double srt = (sqrt(fma(gs, gs, r2)) / gs) / sqrt(ci);
   const double u = pos_root(sg * r.b - xl, srt);
   const double xh = (xl + u) * (1.0 + 64.0 * EPS);
   if (side > 0) { r.lo = xl; r.hi = xh; }
@@ -545,7 +518,7 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
   // of its zero approach the zero from the left: a first step from xh, then steps
   // from wherever it lands, kept inside (y, xh).
   if (jn >= 0 && jn < m && xl > 0.0) {
-    const double rci = recip3(ci);
+    const double rci = 1.0 / ci;
     const double rg = gs * recip(pdiff<KIND>(P.ds[jn], di));
     const double ry = P.ch[jn] * rci * (rg * rg);
     const double rt = (r2 + gs * gs) * rci;
@@ -577,7 +550,7 @@ __host__ __device__ inline BPass b_pass_t(const Prob& P, int i, int side, int ln
         if (!(xn < xhh)) xn = xhh;
         x = xn;
       }
-      r.x0 = sg * fdiv(x, gs);   // back to nu
+      r.x0 = sg * (x / gs);   // back to nu
     }
   }
 #endif
@@ -763,20 +736,6 @@ __host__ __device__ inline double rational_next(double x, double h, double hnois
   return (lo > 0.0 && hi > 16.0 * lo) ? bits_mid(lo, hi) : 0.5 * (lo + hi);
 }
 
-// rational_candidate for kappa = 1, as the step from x, with u = x - pole and
-// ru = 1/u: in units of u, h = c0 - x + psi_x = eta u and the zero u tau away, the
-// fitted equation reads
-//     tau^2 + (2 - b) tau - eta = 0,  b = 1 + psi' + eta,
-// with the discriminant b^2 - 4 psi' (no cancellation: psi' <= 0).  The step itself
-// is what rounds, not the zero u + u tau, so near convergence x + step is the zero
-// to the last bit whatever the step's own few ulps.
-__host__ __device__ inline double rational_step(double h, double dpsi_x, double u, double ru) {
-  const double eta = h * ru;
-  const double b = (1.0 + dpsi_x) + eta, q = (1.0 - dpsi_x) - eta;   // q = 2 - b
-  const double r = fsqrt(fma(b, b, -4.0 * dpsi_x));
-  return u * ((q > 0.0) ? fdiv(2.0 * eta, q + r) : 0.5 * (r - q));
-}
-
 // Lower bound on the zero from the model that keeps the nearest pole exact
 // and replaces the rest of psi_x by its tangent at x:
 //   c0 - t + ry/(t - y) + rest(x) + rest'(x) (t - x),  rest = psi_x - ry/(x - y).
@@ -790,14 +749,14 @@ __host__ __device__ inline double rational_step(double h, double dpsi_x, double 
 // ry, of the order of x^2, overflows when x passes about 2^512, while sry and
 // the coefficients in units of u_x stay in range.  NaN or a value outside the
 // bracket (rounding) is ignored by the caller.
-__host__ __device__ inline double tangent_rest_bound(double y, double h, double dpsi_x, double ux, double rux,
-                                                     double sry) {
-  const double t = sry * rux;   // sqrt(ry) / u_x
+__host__ __device__ inline double tangent_rest_bound(double x, double h, double dpsi_x, double y, double sry) {
+  const double ux = x - y;
+  const double t = sry / ux;   // sqrt(ry) / u_x
   const double beta = h + ux * (1.0 - dpsi_x) - 2.0 * (sry * t);
   const double gamma = fmax(1.0 - dpsi_x - t * t, 1.0);
-  const double bb = beta * rux;
-  const double r = fsqrt(fma(bb, bb, 4.0 * gamma * (t * t)));
-  return y + ux * ((bb >= 0.0) ? fdiv(bb + r, 2.0 * gamma) : fdiv(2.0 * (t * t), r - bb));
+  const double bb = beta / ux;
+  const double r = sqrt(fma(bb, bb, 4.0 * gamma * (t * t)));
+  return y + ux * ((bb >= 0.0) ? (bb + r) / (2.0 * gamma) : 2.0 * (t * t) / (r - bb));
 }
 
 // The step of rational_inverse, which also knows the residue ry of psi_x at
@@ -813,36 +772,28 @@ __host__ __device__ inline double tangent_rest_bound(double y, double h, double 
 // nearest-pole candidate alone advances by a nearly constant factor when the
 // mass of psi_x sits on poles far left of y; the lower bound is what lets the
 // split close in from both sides.  The stopping rules are rational_next's.
-__host__ __device__ inline double bounded_next(double x, double h, double hnoise, double dpsi_x, double d2psi_x,
-                                               double y, double sry, double lo, double hi, int it, int hi_open,
-                                               double& slo, double& shi, int* done) {
+__host__ __device__ inline double bounded_next(double x, double h, double hnoise, double psi_x, double dpsi_x,
+                                               double d2psi_x, double y, double sry, double c0, double lo,
+                                               double hi, int it, int hi_open, double& slo, double& shi,
+                                               int* done) {
   *done = 0;
   if ((hi - lo) <= 4.0 * EPS * fabs(x)) { *done = 1; return x; }
   if (it < RATIONAL_TO_BISECT) {
-    const double uy = x - y;
-    double cand = NAN, step = NAN;
+    double cand = NAN;
     if (d2psi_x > 0) {
-      const double u = fdiv(-2.0 * dpsi_x, d2psi_x);   // x minus the model's pole
-      if (u >= uy && u > 0.0) {
-        step = rational_step(h, dpsi_x, u, fdiv(-0.5 * d2psi_x, dpsi_x));
-        cand = x + step;
-      }
+      const double pe = x + 2.0 * dpsi_x / d2psi_x;
+      if (pe <= y && pe < x) cand = rational_candidate(x, psi_x, dpsi_x, pe, c0, 1);
     }
+    const double up = rational_candidate(x, psi_x, dpsi_x, y, c0, 1);
     const bool second = cand > lo && cand < hi;
-    double up = NAN, ruy = NAN;   // the nearest-pole candidate: the other one's substitute, and an upper bound
-    if (!second) {
-      ruy = fdiv(1.0, uy);
-      step = rational_step(h, dpsi_x, uy, ruy);
-      up = x + step;
-      cand = up;
-    }
-    if (cand == cand && (fabs(step) <= 2.0 * EPS * fabs(cand) || fabs(h) <= hnoise)) {
+    if (!second) cand = up;
+    if (cand == cand && (fabs(cand - x) <= 2.0 * EPS * fabs(cand) || fabs(h) <= hnoise)) {
       *done = 1;
       return (cand > lo && cand < hi) ? cand : x;
     }
 #if AHD_EARLY2 > 0
     if (cand > lo && cand < hi &&
-        fabs(step) <= (second ? ldexp(1.0, -AHD_EARLY2) : ldexp(1.0, -AHD_EARLY1)) * (x - fmax(y, 0.0))) {
+        fabs(cand - x) <= (second ? ldexp(1.0, -AHD_EARLY2) : ldexp(1.0, -AHD_EARLY1)) * (x - fmax(y, 0.0))) {
       *done = 1;
       return cand;
     }
@@ -851,21 +802,17 @@ __host__ __device__ inline double bounded_next(double x, double h, double hnoise
     slo = fmax(slo, lo);
     shi = fmin(shi, hi);
     if (!(slo < shi)) { slo = lo; shi = hi; }
-    if (second) {
-      ruy = fdiv(1.0, uy);
-      up = x + rational_step(h, dpsi_x, uy, ruy);
-    }
-    const double down = tangent_rest_bound(y, h, dpsi_x, uy, ruy, sry);
+    const double down = tangent_rest_bound(x, h, dpsi_x, y, sry);
     // the models agree when the lower bound meets the upper one to within the
     // zero's uncertainty from the rounding of h; then slo == shi
-    const double tol = fdiv(hnoise, 1.0 - dpsi_x);
+    const double tol = hnoise / (1.0 - dpsi_x);
     if (up > slo && up < shi) shi = up;
     if (down > slo && down < shi + tol) slo = fmin(down, shi);
     double xn;
     if (cand > slo && cand < shi) xn = cand;
     else if (slo > 0.0 && shi > 16.0 * slo) xn = bits_mid(slo, shi);
     else if (second) xn = fmin(fmax(cand, slo), shi);
-    else xn = (slo > 0.0 && shi > 2.0 * slo) ? fsqrt(slo) * fsqrt(shi) : 0.5 * (slo + shi);
+    else xn = (slo > 0.0 && shi > 2.0 * slo) ? sqrt(slo * shi) : 0.5 * (slo + shi);
     if (!(xn > lo && xn < hi)) xn = 0.5 * (slo + shi);
     if (xn > lo && xn < hi) return xn;
   }
@@ -895,12 +842,12 @@ template <int KIND>
 __host__ __device__ inline RatConsts rat_consts(const Prob& P, int i, int side, double y) {
   RatConsts c;
   c.sg = (double)side;
-  c.rci = recip3(P.ch[i]);
-  c.src = fdiv(1.0, fsqrt(P.ch[i]));
+  c.rci = 1.0 / P.ch[i];
+  c.src = 1.0 / sqrt(P.ch[i]);
   c.sry = c.src;
   if (y > 0.0) {
     const double e = pdiff<KIND>(P.ds[i - side], P.ds[i]);
-    c.sry = fdiv(fsqrt(P.ch[i - side]) * c.src, fabs(e));
+    c.sry = sqrt(P.ch[i - side]) * c.src / fabs(e);
   }
   return c;
 }
@@ -950,7 +897,7 @@ __host__ __device__ inline bool rat_step(const Prob& P, int i, const RatConsts& 
   if constexpr (WIDE) psi_pass_wide<KIND, false, G>(P, P.ds[i], 0.0, i, nu, ln, gc, s1, s2, s3);
   else psi_pass<KIND, G, false>(P, P.ds[i], 0.0, i, nu, ln, s1, s2, s3);
   if (last) { last[0] = nu; last[1] = s2; last[2] = s3; }   // the sums at the latest point
-  const double rnu = fdiv(1.0, nu);
+  const double rnu = 1.0 / nu;
   const double psi = (s1 + rnu) * c.rci;                       // psi(nu)
   const double dpsi = -(s2 + rnu * rnu) * c.rci;               // psi'(nu)
   const double d2psi = 2.0 * (s3 * rnu + rnu * rnu * rnu) * c.rci;   // psi''(nu)
@@ -960,8 +907,8 @@ __host__ __device__ inline bool rat_step(const Prob& P, int i, const RatConsts& 
   if (h == 0) return true;
   const double hnoise = 8.0 * EPS * (fabs(s.c0) + fabs(s.x) + fabs(psi_x));
   int done = 0;
-  s.x = bounded_next(s.x, h, hnoise, dpsi_x, d2psi_x, s.y, c.sry, s.xlo, s.xhi, s.it, s.hi_open, s.slo, s.shi,
-                     &done);
+  s.x = bounded_next(s.x, h, hnoise, psi_x, dpsi_x, d2psi_x, s.y, c.sry, s.c0, s.xlo, s.xhi, s.it, s.hi_open, s.slo,
+                     s.shi, &done);
   ++s.it;
   return done || s.it >= MAX_RATIONAL + MAX_BISECT;
 }
