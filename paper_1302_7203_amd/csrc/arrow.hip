@@ -11,8 +11,9 @@
 //   k_finish    per eigenvalue: K_nu test (Algorithm 5), repairs (Remarks 1-2, DPR1
 //               re-measure), norm, then its eigenvector, streamed to HBM
 //               (eq. eigenvecAi, Algorithm 4; complex for a Hermitian arrowhead, Sec. 6.1).
-//               Above FIN_MAX k_check, k_repair and k_vec take its place
-//   k_defl      arrowheads above FIN_MAX: the eigenpairs a reducible one deflated (Sec. 1)
+//               Above FIN_MAX k_check, k_repair and k_vec take its place, with the
+//               eigenpairs a reducible arrowhead deflated (Sec. 1) in k_vec's launch,
+//               without vectors in one of their own (k_defl)
 // k_root gives G lanes of a wavefront to each eigenvalue (G = 64: one
 // wavefront per eigenvalue); the vectors are bound by the n^2 FP64 stores.
 
@@ -575,10 +576,37 @@ __global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt
   }
 }
 
-// BLOCK * RPT rows of `cols` columns a block
+// The deflated eigenpairs of a reducible arrowhead (n > FIN_MAX), by `blocks` blocks in
+// turn: placed among the solved ones, whose values are final, and their vectors.  The
+// columns are nobody else's, so with vectors these blocks ride behind the others of the
+// vector launch; a launch of their own (k_defl, without vectors) takes 4.6 us also for
+// the usual irreducible input, where every block returns at once.
+__device__ inline void defl_pairs(const ProbDesc& D, int b, int blocks) {
+  __shared__ int col;
+  const Ws w = ws_view(D.ws, D.n);
+  const int nd = deflated_count(w);
+  for (int s = b; s < nd; s += blocks) {
+    if (threadIdx.x == 0) col = place_deflated(D, w, s);
+    __syncthreads();
+    if (D.V) {
+      double* vc = D.V + (size_t)col * (size_t)D.ldv;
+      for (int r = threadIdx.x; r < D.n; r += BLOCK)
+        __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
+    }
+    __syncthreads();
+  }
+}
+
+// BLOCK * RPT rows of `cols` columns a block; blocks from `tiles` on: the deflated pairs
 template <int KIND, int W, int RPT>
-__global__ __launch_bounds__(BLOCK) void k_vec(ProbDesc D, int row_tiles, int cols) {
+__global__ __launch_bounds__(BLOCK) void k_vec(ProbDesc D, int row_tiles, int cols, int tiles) {
   __shared__ FinStage L;
+  if constexpr (KIND == KIND_ARROW) {
+    if ((int)blockIdx.x >= tiles) {
+      defl_pairs(D, (int)blockIdx.x - tiles, (int)gridDim.x - tiles);
+      return;
+    }
+  }
   const Ws w = ws_view(D.ws, D.n);
   const int ct = blockIdx.x / row_tiles, k0 = ct * cols;
   const int nc = min(D.n - k0, cols);
@@ -828,18 +856,25 @@ __global__ __launch_bounds__(CHECK_BLOCK) void k_check_edges(ProbDesc D, Options
 }
 
 // the columns of the edges and of the repaired eigenvalues (an edge that was
-// repaired is written twice, with the same values), BLOCK * RPT rows of TAIL_COLS a turn
+// repaired is written twice, with the same values), BLOCK * RPT rows of TAIL_COLS a
+// turn; blocks from `takers` on: the deflated pairs
 constexpr int TAIL_COLS = 4;
 
 template <int KIND, int W, int RPT>
-__global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, BigTail T) {
+__global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, BigTail T, int takers) {
   __shared__ FinStage L;
+  if constexpr (KIND == KIND_ARROW) {
+    if ((int)blockIdx.x >= takers) {
+      defl_pairs(D, (int)blockIdx.x - takers, (int)gridDim.x - takers);
+      return;
+    }
+  }
   const Ws w = ws_view(D.ws, D.n);
   const int listed = (int)min(*repair_count(w), (uint32_t)D.n);
   const uint32_t* list = repair_list(w, D.n);
   const int total = 2 * T.blocks + listed;
   const int turns = (total + TAIL_COLS - 1) / TAIL_COLS * row_tiles;
-  for (int turn = blockIdx.x; turn < turns; turn += gridDim.x) {
+  for (int turn = blockIdx.x; turn < turns; turn += takers) {
     const int ct = turn / row_tiles, e0 = ct * TAIL_COLS;
     const int nc = min(total - e0, TAIL_COLS);
     if ((int)threadIdx.x < nc) {
@@ -854,24 +889,7 @@ __global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, B
   }
 }
 
-// The deflated eigenpairs of a reducible arrowhead: placed among the solved ones,
-// whose values are final, and their vectors (n > FIN_MAX).  A block each, in
-// turn; for the usual irreducible input every block returns at once.
-__global__ __launch_bounds__(BLOCK) void k_defl(ProbDesc D) {
-  __shared__ int col;
-  const Ws w = ws_view(D.ws, D.n);
-  const int nd = deflated_count(w);
-  for (int s = blockIdx.x; s < nd; s += gridDim.x) {
-    if (threadIdx.x == 0) col = place_deflated(D, w, s);
-    __syncthreads();
-    if (D.V) {
-      double* vc = D.V + (size_t)col * (size_t)D.ldv;
-      for (int r = threadIdx.x; r < D.n; r += BLOCK)
-        __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
-    }
-    __syncthreads();
-  }
-}
+__global__ __launch_bounds__(BLOCK) void k_defl(ProbDesc D) { defl_pairs(D, (int)blockIdx.x, (int)gridDim.x); }
 
 // ---------------------------------------------------------------------------
 // host side
@@ -1033,20 +1051,23 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
         by_shape([&](auto wd, auto rpt) {
           if constexpr (decltype(rpt)::value >= 4) {
             const int row_tiles = (int)((D.n + (int64_t)BLOCK * sh.rpt - 1) / ((int64_t)BLOCK * sh.rpt));
+            const int defl = KIND == KIND_ARROW ? (int)std::min<int64_t>(D.n - 1, h->cus) : 0;
             if (big) {
-              launch_timed(k_vec_tail<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(2 * h->cus)),
-                           dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, tail);
+              const int takers = 2 * h->cus;
+              launch_timed(k_vec_tail<KIND, decltype(wd)::value, decltype(rpt)::value>,
+                           dim3((unsigned)(takers + defl)), dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, tail,
+                           takers);
               return;
             }
-            const int64_t chunks = (D.n + sh.cols - 1) / sh.cols;
-            launch_timed(k_vec<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(row_tiles * chunks)),
-                         dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, sh.cols);
+            const int tiles = (int)(row_tiles * ((D.n + sh.cols - 1) / sh.cols));
+            launch_timed(k_vec<KIND, decltype(wd)::value, decltype(rpt)::value>, dim3((unsigned)(tiles + defl)),
+                         dim3(BLOCK), 0, st, at(4), at(5), D, row_tiles, sh.cols, tiles);
           }
         });
       }
     }
   }
-  if (KIND == KIND_ARROW && D.n > FIN_MAX)
+  if (KIND == KIND_ARROW && D.n > FIN_MAX && !D.V)
     hipLaunchKernelGGL(k_defl, dim3((unsigned)std::min<int64_t>(D.n - 1, h->cus)), dim3(BLOCK), 0, st, D);
   if (tm) {
     h->ev_set = es;

@@ -20,13 +20,10 @@ PLANS = {
 MAKE = {"arrow": W.uniform_arrow, "dpr1": W.dpr1, "svd": W.svd_arrow, "herm": W.herm_arrow}
 
 
-@pytest.mark.parametrize("lanes", [0, 4, 32])
-@pytest.mark.parametrize("plan", PLANS)
+@pytest.mark.parametrize("plan, lanes", [(p, 0) for p in PLANS] + [("own_or_shared", 4), ("own_or_shared", 32)])
 def test_shared_and_own_items(plan, lanes):
     import torch
     from paper_1302_7203_amd import batch, binding
-    if lanes and plan != "own_or_shared":
-        pytest.skip("fixed lanes: one plan is enough")
     dev = torch.device("cuda", 0)
     rng = np.random.default_rng(23)
     probs = [MAKE[kind](n, rng) for kind, n in PLANS[plan]]

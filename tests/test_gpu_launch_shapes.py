@@ -178,3 +178,24 @@ def test_deflated_beside_repaired_eigenvalues(oracle_lib):
     assert_close(out.lam.cpu().numpy(), ref.lam, "clusters: values")
     assert_close(out.V.cpu().numpy(), ref.vec, "clusters: vectors")
     assert np.array_equal((out.info.cpu().numpy() & 1024) != 0, ref.tau == 0)
+
+
+@pytest.mark.parametrize("n", [4608, 4609, 10200])
+def test_pairs_keep_the_tuned_lanes(n, oracle_lib):
+    """With pairs asked for every order runs the root kernel of the tuned lane count, which the
+    lanes option picks above 4608 for calls without them: bitwise one result, and shift + mu = lambda."""
+    import torch
+    from paper_1302_7203_amd import binding
+    pr = W.graded_arrow(n, np.random.default_rng(n))
+    out = _solve(pr, vectors=False, pairs=True)
+    _sampled(pr, out, vectors=False, count=4)
+    lam = (out.shift + out.mu).cpu().numpy()
+    assert np.all(np.abs(lam - out.lam.cpu().numpy()) <= 2.0 ** -52 * np.abs(lam))
+    if n > 4608:
+        lanes = [g for m, g in zip(*binding.read_tuned()["single"]) if n <= m][0]
+        binding.set_option(binding.OPT_LANES, lanes)
+        try:
+            same = _solve(pr, vectors=False)
+        finally:
+            binding.set_option(binding.OPT_LANES, 0)
+        assert torch.equal(same.lam, out.lam)
