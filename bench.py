@@ -207,7 +207,7 @@ def batched_headline(args, workloads, dev, steps, cpu=True):
                       "root_finder": args.root},
            "stages_ms": {k: float(v) for k, v in zip(("prologue", "root", "check", "repair", "vectors"), stages)},
            "stage_timing": {"runs": args.timing_runs,
-                            "how": "an eager plan of the same problems whose five kernels stamp HIP events by their "
+                            "how": "an eager plan of the same problems whose kernels stamp HIP events by their "
                                    "own dispatches (hipExtLaunchKernel) on the plan's stream; its outputs are "
                                    "bitwise those of the timed graph plan: " + str(same_eager)},
            "counters": cnt, "info_counts": info_counts, "roofline": roof, "roofline_vector": roof_v,
@@ -484,15 +484,22 @@ def single_run(args, workload, binding, workloads, dev, steps, cpu=True):
     recount = m * (f_iter * cnt["root_bisect"] + F_DD * cnt["root_dd"] + F_SELECT * cnt["root_plain"])
     root_flops = m * (W_FIXED * float(n) + W_ITER * cnt["root_bisect"])
     t_root = stages[2] * 1e-3
-    roof = {"kernel": "k_root", "bound": "alu", "achieved": root_flops / t_root / 1e12,
-            "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s", "traffic": profiled_traffic(workload, "k_root<"),
+    # orders whose vectors the root kernel writes (a tail kernel adds the rest), and those whose
+    # check, repairs and vectors are one kernel
+    big, small = n > 4608, n <= 1280
+    root_name = "k_root_big" if big else "k_root"
+    roof = {"kernel": root_name, "bound": "alu", "achieved": root_flops / t_root / 1e12,
+            "peak": PEAK_FP64_VECTOR / 1e12, "unit": "TFLOP/s",
+            "traffic": profiled_traffic(workload, root_name + "<"),
             "flops_per_launch": root_flops, "per_unit": ROOF_UNIT,
             "recount": {"flops_per_launch": recount, "achieved": recount / t_root / 1e12,
                         "frac": recount / t_root / PEAK_FP64_VECTOR}}
     roof["frac"] = roof["achieved"] / roof["peak"]
     vec_bytes = 8.0 * n * n + 16.0 * n
-    roof_v = {"kernel": "k_vec", "bound": "hbm", "achieved": vec_bytes / (stages[4] * 1e-3) / 1e9,
-              "peak": PEAK_HBM / 1e9, "unit": "GB/s", "traffic": profiled_traffic(workload, "k_vec<"),
+    t_vec = (stages[4] + (stages[2] if big else 0.0)) * 1e-3
+    roof_v = {"kernel": "k_root_big + k_vec_tail" if big else "k_finish" if small else "k_vec", "bound": "hbm",
+              "achieved": vec_bytes / t_vec / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
+              "traffic": None if big else profiled_traffic(workload, "k_finish<" if small else "k_vec<"),
               "bytes_per_launch": vec_bytes}
     roof_v["frac"] = roof_v["achieved"] / roof_v["peak"]
     res = {"value": n * steps / elapsed, "unit": "eigenpairs/s", "steps": steps,
@@ -503,7 +510,8 @@ def single_run(args, workload, binding, workloads, dev, steps, cpu=True):
            "stage_timing": {"sampled_steps": sampled["sampled_steps"], "every": max(1, args.timing_every),
                             "how": "HIP events stamped by the kernels' own dispatches (hipExtLaunchKernel) on the "
                                    "solve's stream, on every k-th timed step; root and vectors are the kernels' "
-                                   "durations"},
+                                   "durations; n <= 1280: check and vectors are one kernel, under vectors; "
+                                   "n > 4608: root writes most of the vectors"},
            "counters": cnt, "roofline": roof, "roofline_vector": roof_v}
     info = out.info.cpu().numpy().astype(np.uint32)
     res["info_counts"] = {name: int(np.sum((info & bit) != 0)) for name, bit in
