@@ -707,7 +707,7 @@ __device__ __forceinline__ void wave_columns(const ProbDesc& D, uint64_t mask, i
 // HOT 1: poles and weights in LDS; HOT 2: the poles alone, where both do not fit.
 // At n = 16384 the root stage was bound by the L2: 72 bytes a term, 860 us at 22
 // TB/s; with the poles in LDS 40 bytes, and bound by issued instructions, 603 us
-// (n = 8192 285 -> 209 us, 5000 120 -> 101 us).  With the columns 875 us, where
+// (n = 8192 285 -> 209 us, 5000 120 -> 101 us).  With the columns 890 us, where
 // root stage and vectors took 860 + 387: a writing wavefront is one fewer computing
 // (two or eight writers at a time: 900 and 920 us).
 constexpr int BIG_BLOCK = 1024;

@@ -5,8 +5,8 @@
 //   k_b_root    persistent: every wavefront takes (problem, eigenvalue-group)
 //               items from an atomic queue and runs the first pass (shift,
 //               b, root of the inverse) on them, reading the problem's poles
-//               (and weights) from its own LDS slice where they fit, and
-//               regrouping unfinished roots onto wider lane groups; problems
+//               (and weights) from its own LDS slice where they fit, for the
+//               larger orders from the slices of the whole block, and regrouping unfinished roots onto wider lane groups; problems
 //               are queued by decreasing order n so the long items start first
 //   k_b_check   the K_nu test and the outputs, one lane per eigenvalue; the few that
 //               need O(n) passes (Remark 2, the DPR1 re-measure) go to the plan's
