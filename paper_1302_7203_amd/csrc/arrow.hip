@@ -371,13 +371,8 @@ struct FinStage {
   double pv[FIN_COLS], sf[FIN_COLS], mu[FIN_COLS], inrm[FIN_COLS], sig[FIN_COLS];
   int col[FIN_COLS];     // output column, -1: none (past a deflated problem's order, or a redo block's)
   int redo[BLOCK];       // eigenvalues this block re-solves
-  int redo_count, above;
+  int redo_count;
 };
-
-// Relative distance (to the pole's and mu's size) within which a first-pass
-// eigenvalue that still needs a repair may lie on the other side of a deflated one:
-// such values are good to about K_nu eps, or eps of the pole near the origin.
-constexpr double DEFL_NEAR = 1e-6;
 
 template <int KIND, int W, int RPT>
 __device__ inline void finish_rows(const ProbDesc& D, int rt, int nc, const FinStage& L) {
@@ -503,46 +498,34 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
     if (redo) __syncthreads();
   }
   if constexpr (KIND == KIND_ARROW) {
-    // The deflated eigenpairs, in turn.  One's column counts the eigenvalues at or
-    // above it: those of the first pass, which are final where no repair is due and
-    // tell the order elsewhere too unless they are within DEFL_NEAR of it; these few
-    // are re-solved here as well (the same values as their own block's).
+    // The deflated eigenpairs, in turn.  The one eigenvalue that decides a pair's
+    // column is re-solved here as well where it is to be repaired (the same values as
+    // its own block's).  The poles above the pair's are counted by the whole block, as
+    // a search would be a chain of loads (62 us a call at n = 300, counted 57).
     const int nd = redo ? deflated_count(w) : 0;
-    const int np = reduced_m(w) + 1;
+    const int mr = reduced_m(w);
     for (int s = (int)blockIdx.x; s < nd; s += redo_blocks) {
       const double v = w.dv[s];
-      if (t == 0) L.above = 0;
-      for (int base = 0; base < np; base += BLOCK) {
-        if (t == 0) L.redo_count = 0;
-        __syncthreads();
-        const int k = base + t;
-        if (k < np) {
-          const double lam = dd_to_d(dd_add_d(dd_add_d(pval_dd<SK>(w.pv1[k]), 0.0), w.mu1[k]));
-          const bool near = fabs(lam - v) <= DEFL_NEAR * (fabs(w.pv1[k]) + fabs(w.mu1[k]));
-          if (near && check_body<SK, 1, false, DEFER_BLOCK>(D, opt, k, 0, nullptr, nullptr, false))
-            L.redo[atomicAdd(&L.redo_count, 1)] = k;
-          else if (lam >= v) atomicAdd(&L.above, 1);
-        }
-        __syncthreads();
-        const int again = L.redo_count;
-        if (again > 0 && !staged) {
+      double d[FIN_MAX / BLOCK];
+#pragma unroll
+      for (int q = 0; q < FIN_MAX / BLOCK; ++q) d[q] = t + q * BLOCK < mr ? w.ds[t + q * BLOCK] : NAN;
+      int above = 0;
+#pragma unroll
+      for (int q = 0; q < FIN_MAX / BLOCK; ++q) above += __syncthreads_count(d[q] >= v);
+      const int col = s + deflated_above<SK>(D, opt, w, v, above, [&](int k) {
+        if (!staged) {
           stage_hot(D, lds);
           staged = true;
         }
-        for (int q = 0; q < again; ++q) {
-          check_body<SK, BLOCK, true>(D, opt, L.redo[q], t, lds, lds + sorted_count(D));
-          if (t == 0 && w.lr[L.redo[q]] >= v) L.above += 1;   // thread 0 wrote it
-        }
+        check_body<SK, BLOCK, true>(D, opt, k, t, lds, lds + sorted_count(D));
         __syncthreads();
-      }
-      const int col = s + L.above;
+      });
       if (t == 0) place_deflated_at(D, w, s, col);
       if (D.V) {
         double* vc = D.V + (size_t)col * (size_t)D.ldv;
         for (int r = t; r < D.n; r += BLOCK)
           __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
       }
-      __syncthreads();
     }
   }
 }

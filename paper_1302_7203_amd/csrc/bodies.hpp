@@ -58,7 +58,7 @@ struct Ws {
   // deflation of a reducible arrowhead (Sec. 1): hdr[8] = poles m' of the
   // irreducible problem that the root and check stages solve, hdr[9] = number
   // of deflated eigenpairs, hdr[10] = completion count of the repair launch
-  double* lr;       // the irreducible problem's eigenvalues, by its index
+  double* lr;       // the irreducible problem's eigenvalues (merge_key), by its index
   double* dv;       // deflated eigenvalues, descending
   double* da;       // per deflated eigenpair: factor of the earlier rows of its run ...
   double* db;       // ... and its own entry (see deflate_run)
@@ -372,8 +372,19 @@ __host__ __device__ inline double deflated_entry(const Ws& w, int s, int j, doub
 
 // Output columns are the merge of the reduced eigenvalues (descending, as
 // computed) with the deflated ones (descending); on a tie the reduced one
-// comes first.  Reduced eigenvalue k goes to column k + #{deflated > lambda_k},
-// deflated item s to column s + #{reduced >= delta_s} (which place_deflated returns).
+// comes first.  Reduced eigenvalue k goes to column k + #{deflated > key_k},
+// deflated item s to column s + #{key >= delta_s} (which place_deflated returns).
+//
+// key_k is lambda_k, held between the reduced poles on either side of it, where
+// it lies in exact arithmetic: so the keys descend whatever an eigenvalue's
+// accuracy (remedies off, an extreme tau_nu), both sides decide by the same keys,
+// and the columns are a permutation.  An accurate lambda_k is its own key.
+__host__ __device__ inline double merge_key(const Ws& w, int k, double lam) {
+  if (k < reduced_m(w)) lam = fmax(lam, w.ds[k]);
+  if (k > 0) lam = fmin(lam, w.ds[k - 1]);
+  return lam;
+}
+
 __host__ __device__ inline void place_deflated_at(const ProbDesc& D, const Ws& w, int s, int col) {
   const double v = w.dv[s];
   D.lam[col] = v;
@@ -615,8 +626,12 @@ __host__ __device__ inline void defer_repair(const Ws& w, int64_t n, int k, int 
 
 constexpr int DEFER_NONE = 0, DEFER_BLOCK = 1, DEFER_NEAR_ZERO = 2, DEFER_WAVE = 3;
 
+// Always inlined: as a call it took the problem by address (through scratch memory),
+// and around one such call the compiler kept the caller's registers in accumulation
+// registers by copies placed before the join of a skipped branch restored the exec
+// mask, where they copy nothing (k_finish then went on with stale addresses).
 template <int KIND, int G, bool HOT = false, int DEFER = DEFER_NONE>
-__host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt, int k, int ln,
+__host__ __device__ __forceinline__ bool check_body(const ProbDesc& D, const Options& opt, int k, int ln,
                                            const double* hot_d = nullptr, const double* hot_c = nullptr,
                                            bool commit = true) {
   const Ws w = ws_view(D.ws, D.n);
@@ -784,8 +799,9 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
     if constexpr (KIND == KIND_ARROW) {
       const int nd = deflated_count(w);
       if (nd > 0) {
-        col = k + count_above(w.dv, nd, lam, false);
-        w.lr[k] = lam;
+        const double key = merge_key(w, k, lam);
+        col = k + count_above(w.dv, nd, key, false);
+        w.lr[k] = key;
         w.cm[col] = -1;
       }
     }
@@ -811,6 +827,25 @@ __host__ __device__ inline bool check_body(const ProbDesc& D, const Options& opt
     if (D.info) D.info[col] = fl;
   }
   return false;
+}
+
+// #{key >= v} of place_deflated for a deflated value v, before the reduced
+// eigenvalues are all final: those of the reduced poles at or above v are above
+// it and those of the poles below v but the first are below, whatever their
+// values, so only eigenvalue b = #{reduced poles >= v} is compared.  Its first
+// pass is final unless the check asks for a repair, which `resolve(b)` then runs
+// (check_body with DEFER_NONE, and a barrier where several threads share the work).
+template <int KIND, class F>
+__host__ __device__ inline int deflated_above(const ProbDesc& D, const Options& opt, const Ws& w, double v, int b,
+                                              F&& resolve) {
+  double key;
+  if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, b, 0, nullptr, nullptr, false)) {
+    resolve(b);
+    key = w.lr[b];
+  } else {
+    key = merge_key(w, b, dd_to_d(dd_add_d(dd_add_d(pval_dd<KIND>(w.pv1[b]), 0.0), w.mu1[b])));
+  }
+  return b + (key >= v ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------

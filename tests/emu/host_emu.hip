@@ -14,7 +14,9 @@
 using namespace ahd;
 
 // 1: the batched plan's check stage -- Remark 2 and the DPR1 re-measure in the
-// check itself, eigenvalues near the origin listed and repaired afterwards
+// check itself, eigenvalues near the origin listed and repaired afterwards;
+// 2: the single launch that finishes small problems -- deflated pairs placed while
+// the eigenvalues that need a repair are still unsolved
 static int g_batch_check = 0;
 
 template <int KIND>
@@ -68,7 +70,20 @@ static void run(ProbDesc D, const Options& opt, double* U) {
   constexpr int SK = KIND == KIND_HERM ? KIND_ARROW : KIND;
 #pragma omp parallel for schedule(dynamic, 4)
   for (int k = 0; k < D.n; ++k) root_body<SK, 1>(D, opt, k, 0);
-  if (g_batch_check) {
+  const int nd = deflated_count(w);
+  bool placed = false;
+  if (g_batch_check == 2) {
+    std::vector<int> again;
+    for (int k = 0; k < D.n; ++k)
+      if (check_body<SK, 1, false, DEFER_BLOCK>(D, opt, k, 0)) again.push_back(k);
+    if constexpr (KIND == KIND_ARROW) {
+      for (int s = 0; s < nd; ++s)
+        place_deflated_at(D, w, s, s + deflated_above<SK>(D, opt, w, w.dv[s], count_above(w.ds, reduced_m(w), w.dv[s], true),
+                                                          [&](int k) { check_body<SK, 1>(D, opt, k, 0); }));
+      placed = true;
+    }
+    for (int k : again) check_body<SK, 1>(D, opt, k, 0);
+  } else if (g_batch_check) {
     // as the batched check stage: Remark 2 and the DPR1 re-measure gathered and
     // re-run (DEFER_WAVE, then DEFER_NEAR_ZERO), Remark 1 listed for the repairs
     *repair_count(w) = 0u;
@@ -83,8 +98,8 @@ static void run(ProbDesc D, const Options& opt, double* U) {
 #pragma omp parallel for schedule(dynamic, 4)
     for (int k = 0; k < D.n; ++k) check_body<SK, 1>(D, opt, k, 0);
   }
-  const int nd = deflated_count(w);
-  for (int s = 0; s < nd; ++s) place_deflated(D, w, s);
+  if (!placed)
+    for (int s = 0; s < nd; ++s) place_deflated(D, w, s);
   if (KIND == KIND_HERM && D.V) {
 #pragma omp parallel for schedule(static)
     for (int k = 0; k < D.n; ++k)
