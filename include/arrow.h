@@ -143,8 +143,10 @@ int arrow_eig(arrow_handle_t h, int64_t n, const double* d, const double* z, dou
  * allocating routine.  The scratch is shared by every arrow_eig_noalloc call on
  * that device, through any handle: calls whose executions overlap on one
  * device (different streams, or different host threads) race and give wrong
- * results; calls ordered on one stream are safe.  Each call's kernels set up
- * every scratch word they read (the last call's contents stay behind).
+ * results; calls ordered on one stream are safe, also
+ * after calls that overlapped.  Each call's kernels set up every scratch word
+ * they read, but for one count that each call leaves at 0 (the rest of the last
+ * call's contents stay behind).
  */
 #define ARROW_NOALLOC_N_MAX 32768
 int arrow_eig_noalloc(arrow_handle_t h, int64_t n, const double* d, const double* z, double alpha,

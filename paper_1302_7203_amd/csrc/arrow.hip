@@ -69,6 +69,7 @@ constexpr int PREP_ONE = 256;     // poles one block ranks alone: 64 comparisons
 constexpr int PREP_MAX = 16384;   // the blocks' order checks read n^2 / 64 keys from the L2
 constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (its rank is none)
 
+// blocks of the sort that are done: 0 between calls
 __host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
 // 1 when the caller's poles already are in the sorted order
 __host__ __device__ inline uint32_t* in_order(const Ws& w) { return (uint32_t*)(w.hdr + 11); }
@@ -154,7 +155,9 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
   if constexpr (!ONE) {
     // behind the barrier one thread releases the block's entries at device scope
     // (a write-back of the L2 a wavefront, so one is enough) and counts the block
-    // in (the count wraps to 0 for the next call); the last block acquires
+    // in; the last block acquires.  The count wraps to 0, and a later launch of every
+    // call (k_finish, k_repair) stores 0 as well: calls that overlapped in one workspace
+    // may leave another value, and the first one ordered behind them must find 0
     __syncthreads();
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -294,7 +297,6 @@ __global__ __launch_bounds__(SORT_BLOCK) void k_sort(ProbDesc D, int chunk, int 
   __syncthreads();
   if (!last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (threadIdx.x == 0) *sort_done(w) = 0u;   // as k_prep leaves it
   for (int q = threadIdx.x; q < ms; q += SORT_BLOCK) {
     const uint32_t raw = __hip_atomic_load(&rank[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int r = (int)(raw & 0x3fffffffu);
@@ -470,6 +472,7 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
   const int k0 = redo ? (int)blockIdx.x : ((int)blockIdx.x - redo_blocks) * cols;
   const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);   // at most FIN_MAX / redo_blocks, cols
   if (t == 0) L.redo_count = 0;
+  if (blockIdx.x == 0 && t == 0) *sort_done(w) = 0u;   // for the next call
   __syncthreads();
   if (t < mine) {
     const int k = k0 + t * step;
@@ -549,6 +552,7 @@ __global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt
   extern __shared__ double lds[];
   const Ws w = ws_view(D.ws, D.n);
   const uint32_t count = min(*repair_count(w), (uint32_t)D.n);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *sort_done(w) = 0u;   // for the next call
   if (blockIdx.x >= count) return;
   if constexpr (STAGE) stage_hot(D, lds);
   const uint32_t* list = repair_list(w, D.n);

@@ -70,7 +70,7 @@ static inline int ensure_ws(arrow_handle_t h, size_t doubles) {
     h->ws = nullptr;
     return ARROW_ERR_NOMEM;
   }
-  // the header's completion counts start at 0; each call leaves them there
+  // the sort's completion count starts at 0; each call leaves it there
   if (hipMemsetAsync(h->ws, 0, 16 * sizeof(double), h->stream) != hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess) {
     (void)hipFree(h->ws);
