@@ -115,6 +115,9 @@ size_t arrow_workspace_size(int64_t n);
  *   shift, mu: optional (null allowed); lambda_k = shift_k + mu_k exactly in
  *           real arithmetic, where shift_k is the pole the eigenvalue was
  *           computed from (Remark 3); this pair carries ~32 digits.
+ *           Asking for either of them above n = 4608 selects the first pass's
+ *           kernel of the lanes table (arrow_set_lanes_table), so lambda may
+ *           differ in its last bits from a call without them.
  *   info:   optional, n uint32 ARROW_INFO_* bits.
  * Reducible input (Sec. 1: some z_j = 0, or d_i = d_j) is deflated on the
  * device: a pole d_j with z_j = 0 is an eigenvalue with the unit vector e_j;
