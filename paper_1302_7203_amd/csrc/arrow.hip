@@ -470,7 +470,7 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
   const bool redo = (int)blockIdx.x < redo_blocks;
   const int step = redo ? redo_blocks : 1;
   const int k0 = redo ? (int)blockIdx.x : ((int)blockIdx.x - redo_blocks) * cols;
-  const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);   // at most FIN_MAX / redo_blocks, cols
+  const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);   // at most BLOCK (finish_redo_blocks), cols
   if (t == 0) L.redo_count = 0;
   if (blockIdx.x == 0 && t == 0) *sort_done(w) = 0u;   // for the next call
   __syncthreads();
@@ -1013,7 +1013,7 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
       else { if (pair) go(two(), std::integral_constant<int, 2>()); else go(one(), std::integral_constant<int, 2>()); }
     };
     if (D.n <= FIN_MAX) {
-      const int redo_blocks = (int)std::min<int64_t>(D.n, h->cus);
+      const int redo_blocks = finish_redo_blocks(D.n, h->cus, BLOCK);
       const int cols = D.V ? sh.cols : FIN_VALUES;
       const dim3 grid((unsigned)(redo_blocks + (D.n + cols - 1) / cols));
       by_shape([&](auto wd, auto rpt) {

@@ -96,6 +96,14 @@ static inline int single_lanes(const arrow_handle_s* h, int64_t n) {
   return table_lookup(h, ARROW_SCHEDULE_SINGLE, n, g);
 }
 
+// Blocks of the launch that finishes a small problem that re-solve its listed
+// eigenvalues: one a compute unit, and no fewer than let a block of `block` threads
+// ask each of its eigenvalues with a thread of its own.
+static inline int finish_redo_blocks(int64_t n, int cus, int block) {
+  const int64_t a = n < cus ? n : cus, b = (n + block - 1) / block;
+  return (int)(a > b ? a : b);
+}
+
 // all launches of one single-problem solve (defined with the single-problem kernels)
 int launch_single(arrow_handle_t h, const ahd::ProbDesc& D);
 

@@ -35,6 +35,8 @@ def _load():
                                 ctypes.c_double, ctypes.c_double, ctypes.c_int, ctypes.c_int, P, ctypes.c_int, P,
                                 ctypes.c_double, P]
         L.emu_solve.restype = ctypes.c_int
+        L.emu_finish_redo_blocks.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+        L.emu_finish_redo_blocks.restype = ctypes.c_int
         L.emu_set_batch_check.argtypes = [ctypes.c_int]
         L.emu_set_batch_check.restype = None
         _lib = L
@@ -55,6 +57,11 @@ def set_finish_check(on: bool):
     """Run the check as the launch that finishes small single problems does: repairs left to the
     end, deflated pairs placed before them."""
     _load().emu_set_batch_check(2 if on else 0)
+
+
+def finish_redo_blocks(n: int, cus: int, block: int) -> int:
+    """Blocks that re-solve the listed eigenvalues of a small single problem."""
+    return _load().emu_finish_redo_blocks(n, cus, block)
 
 
 def solve(kind, d, z, scalar, vectors=True, tau_nu=100.0, tau_zero=10.0, fp64_b=0, remedies=1, root=1, tau_b=0.0):

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../paper_1302_7203_amd/csrc/bodies.hpp"
+#include "../../paper_1302_7203_amd/csrc/host.hpp"
 
 using namespace ahd;
 
@@ -124,6 +125,8 @@ static void run(ProbDesc D, const Options& opt, double* U) {
 }
 
 extern "C" void emu_set_batch_check(int on) { g_batch_check = on; }
+
+extern "C" int emu_finish_redo_blocks(int64_t n, int cus, int block) { return finish_redo_blocks(n, cus, block); }
 
 extern "C" int emu_solve(int kind, int64_t n, const double* d, const double* z, double scalar, double* lam,
                          double* V, double* U, double* shift, double* mu, uint32_t* info, double tau_nu,
