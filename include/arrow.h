@@ -320,9 +320,9 @@ int arrow_solve_batched(arrow_handle_t h, int64_t count, const arrow_desc_t* des
  *   scope ARROW_SCHEDULE_SINGLE: arrow_eig / dpr1_eig / arrow_svd calls;
  *     lanes 1, 2, 4, ..., 64.  n beyond the table and entries = 0 use the
  *     built-in rule (about 8 pole terms per lane, at most 64 lanes).  The
- *     option ARROW_OPT_LANES, when nonzero, overrides the table.  From n = 4609
- *     while the poles fit a compute unit's LDS (n to about 20200) a kernel of its
- *     own takes 64 lanes whatever the table says, unless that option is set.
+ *     option ARROW_OPT_LANES, when nonzero, overrides the table.  Where they leave
+ *     64 lanes, a kernel of its own takes calls without shift pairs from n = 4609
+ *     on while the poles fit a compute unit's LDS (n to about 20200).
  *   scope ARROW_SCHEDULE_BATCH: plans created afterwards; lanes 4, ..., 64;
  *     n beyond the table uses 64; entries = 0 restores the built-in table
  *     {24: 4, 48: 8, 96: 16, 192: 32, larger: 64}.
@@ -335,6 +335,13 @@ int arrow_solve_batched(arrow_handle_t h, int64_t count, const arrow_desc_t* des
 #define ARROW_SCHEDULE_SINGLE 0
 #define ARROW_SCHEDULE_BATCH 1
 int arrow_set_lanes_table(arrow_handle_t h, int scope, int32_t entries, const int32_t* n_max, const int32_t* lanes);
+
+/* arrow_set_lanes_table of scope ARROW_SCHEDULE_SINGLE for a table of measured
+ * defaults rather than a caller's wish: the kernel that takes large problems on 64
+ * lanes (above) does so whatever this table says, and the table's counts hold for
+ * the rest.  A later arrow_set_lanes_table replaces it.  Returns as that call does
+ * (-2 does not occur). */
+int arrow_set_default_lanes(arrow_handle_t h, int32_t entries, const int32_t* n_max, const int32_t* lanes);
 
 /*
  * Diagnostics of the most recent single-problem call on this handle.

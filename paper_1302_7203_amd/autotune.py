@@ -7,15 +7,17 @@ loops).  The best G depends on the order n, on how many eigenvalues are in
 flight (one problem, or a whole batch) and on the device, so it is measured:
 
 * single problems: one arrowhead solve (all eigenvalues and vectors) of each
-  order in SINGLE_NS, timed for every G;
+  order in SINGLE_NS, timed for every G (above n = 4608 the kernel that takes a
+  fixed G: calls that ask for no shift pairs run the large problems' kernel there,
+  which these entries do not choose);
 * batches: a mixed batch (60% arrowhead, 25% DPR1, 15% SVD) of orders drawn
   log-uniformly in each bucket of BATCH_BUCKETS, about BATCH_PAIRS
   eigenpairs in all, one hipGraph-captured plan per G.
 
 The fastest G per size becomes a table entry (n_max, lanes); the tables are
 written as JSON (binding.TUNED_PATH by default), and the binding installs them
-into every handle it creates through arrow_set_lanes_table.  Results do not
-depend on the table beyond rounding: every G meets the same accuracy bar.
+into every handle it creates (arrow_set_default_lanes, arrow_set_lanes_table).
+Results do not depend on the table beyond rounding: every G meets the same accuracy bar.
 
     python -m paper_1302_7203_amd.autotune [--out PATH] [--reps 5] [--quick]
 """

@@ -84,6 +84,7 @@ def lib():
                 L.arrow_last_counters.argtypes = [P, ctypes.POINTER(ctypes.c_int64)]
                 L.arrow_conditions.argtypes = [P, P, P]
                 L.arrow_set_lanes_table.argtypes = [P, I, ctypes.c_int32, P, P]
+                L.arrow_set_default_lanes.argtypes = [P, ctypes.c_int32, P, P]
                 L.arrow_probe_fma.argtypes = [P, I64, I, P]
                 L.arrow_probe_fill.argtypes = [P, I64, D, P]
                 L.arrow_probe_copy.argtypes = [P, P, I64, P]
@@ -92,7 +93,7 @@ def lib():
                           "arrow_create", "arrow_destroy", "arrow_set_stream", "arrow_set_option",
                           "arrow_eig", "arrow_eig_noalloc", "arrow_eig_herm", "tridiag_eig", "dpr1_eig", "arrow_svd",
                           "arrow_last_timing", "arrow_timing_of", "arrow_last_counters", "arrow_conditions",
-                          "arrow_set_lanes_table"):
+                          "arrow_set_lanes_table", "arrow_set_default_lanes"):
                     getattr(L, f).restype = ctypes.c_int
                 _lib = L
     return _lib
@@ -124,19 +125,23 @@ def read_tuned(path: str = TUNED_PATH) -> dict | None:
     return out
 
 
+def _int32s(xs):
+    return (ctypes.c_int32 * max(1, len(xs)))(*[int(x) for x in xs])
+
+
 def set_lanes_table(scope: int, n_max, lanes, h: ctypes.c_void_p | None = None, device=None):
     """Install a lanes-per-eigenvalue table (arrow_set_lanes_table); empty lists restore the default."""
     h = handle(device) if h is None else h
-    a = (ctypes.c_int32 * max(1, len(n_max)))(*[int(x) for x in n_max])
-    b = (ctypes.c_int32 * max(1, len(lanes)))(*[int(x) for x in lanes])
-    _check(lib().arrow_set_lanes_table(h, scope, len(n_max), a, b), "arrow_set_lanes_table")
+    _check(lib().arrow_set_lanes_table(h, scope, len(n_max), _int32s(n_max), _int32s(lanes)), "arrow_set_lanes_table")
 
 
 def apply_tuned(h: ctypes.c_void_p, path: str = TUNED_PATH):
-    """Load the autotuned tables, if any, into handle h."""
+    """Load the autotuned tables, if any, into handle h: the single problems' as defaults, which
+    leave the large ones to their own kernel (arrow_set_default_lanes)."""
     t = read_tuned(path)
     if t is not None:
-        set_lanes_table(SCHEDULE_SINGLE, *t["single"], h=h)
+        n_max, lanes = t["single"]
+        _check(lib().arrow_set_default_lanes(h, len(n_max), _int32s(n_max), _int32s(lanes)), "arrow_set_default_lanes")
         set_lanes_table(SCHEDULE_BATCH, *t["batch"], h=h)
 
 

@@ -979,14 +979,14 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
   // the stages between take up the dispatch gaps
   const size_t hot = (size_t)(ms + D.n - 1) * sizeof(double);
   // the large problems' kernel, where at least the poles fit a compute unit's LDS
-  // and nobody asked for another number of lanes
+  // and the caller did not ask for another number of lanes
   const int each = (int)std::max<int64_t>(BIG_EACH, (D.n + h->cus - 1) / h->cus);
   const size_t poles = (size_t)ms * sizeof(double), extra = big_lds(each) + 1024;   // and a little static LDS
   // Not where the caller takes the shift pairs or either half of them: the shift of Remark 2(b) is formed from
   // the first pass's mu, of which an ill-conditioned eigenvalue has few digits, and the
   // pair's mu shows all of them (20 decades, n = 6000: 5e-9 between two lane counts, the
   // eigenvalues equal).  The pairs stay those of the tuned lane count.
-  const bool big = D.n > BIG_MIN && h->lanes == 0 && !D.shift && !D.mu && poles + extra <= h->lds_max;
+  const bool big = D.n > BIG_MIN && large_kernel_lanes(h, D.n) && !D.shift && !D.mu && poles + extra <= h->lds_max;
   const BigTail tail{each, (D.n + each - 1) / each};
   const bool hot_both = hot + extra <= h->lds_max;
   const bool pair_rows = KIND != KIND_HERM && (D.n % 2 == 0) && (D.ldv % 2 == 0) && (((uintptr_t)D.V & 15) == 0) &&

@@ -606,12 +606,19 @@ int arrow_set_lanes_table(arrow_handle_t h, int scope, int32_t entries, const in
     if (g < gmin || g > 64 || (g & (g - 1)) != 0) return -5;
     if (n_max[e] < 1 || (e > 0 && n_max[e] <= n_max[e - 1])) return -4;
   }
+  if (scope == ARROW_SCHEDULE_SINGLE) h->tab_default = 0;
   h->ntab[scope] = entries;
   for (int e = 0; e < entries; ++e) {
     h->tab_n[scope][e] = n_max[e];
     h->tab_g[scope][e] = lanes[e];
   }
   return ARROW_OK;
+}
+
+int arrow_set_default_lanes(arrow_handle_t h, int32_t entries, const int32_t* n_max, const int32_t* lanes) {
+  const int rc = arrow_set_lanes_table(h, ARROW_SCHEDULE_SINGLE, entries, n_max, lanes);
+  if (rc == ARROW_OK) h->tab_default = 1;
+  return rc;
 }
 
 int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* descs, const double* in_pool,

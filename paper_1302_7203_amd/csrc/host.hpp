@@ -33,6 +33,7 @@ struct arrow_handle_s {
   int ntab[2];
   int32_t tab_n[2][LANE_TABLE_MAX];
   int32_t tab_g[2][LANE_TABLE_MAX];
+  int tab_default;    // the single-problem table came by arrow_set_default_lanes
   void* blas;         // rocBLAS handle of tridiag_eig's GEMMs, made on first use
   void* td_ws;        // tridiag_eig's device buffers (grown on demand, kept)
   size_t td_cap;      // bytes
@@ -94,6 +95,12 @@ static inline int single_lanes(const arrow_handle_s* h, int64_t n) {
   int g = 1;
   while (g < 64 && g < n / 8) g <<= 1;
   return table_lookup(h, ARROW_SCHEDULE_SINGLE, n, g);
+}
+
+// whether the large problems' kernel, 64 lanes per eigenvalue, may take a call of order
+// n: a caller's own lane count comes first (64 is its own), a default table does not
+static inline bool large_kernel_lanes(const arrow_handle_s* h, int64_t n) {
+  return h->lanes == 0 && (h->tab_default || single_lanes(h, n) == 64);
 }
 
 // Blocks of the launch that finishes a small problem that re-solve its listed
