@@ -67,7 +67,7 @@ constexpr int PREP_BLOCK = 1024;
 constexpr int PREP_WAVES = PREP_BLOCK / 64;
 constexpr int PREP_ONE = 256;     // poles one block ranks alone: 64 comparisons a lane
 constexpr int PREP_MAX = 16384;   // the blocks' order checks read n^2 / 64 keys from the L2
-constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (its rank is none)
+constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (it has no rank and no sorted entry)
 
 // blocks of the sort that are done: 0 between calls
 __host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
@@ -147,9 +147,9 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     r = 0;
     for (int q = 0; q < shares; ++q) r += part[q * groups + grp][lane];
   }
-  if (has) {   // r < ms: the other keys in front of j's
+  if (has) w.st[j] = input_status_vals<KIND>(dj, re, im, false) | (kj == kj ? 0u : ST_NAN);
+  if (has && kj == kj) {   // r < ms: the other keys in front of j's
     const SortedEntry e = put_sorted_vals<KIND>(w, r, j, (KIND == KIND_DPR1 && D.neg) ? -dj : dj, re, im);
-    w.st[j] = input_status_vals<KIND>(dj, re, im, false) | (kj == kj ? 0u : ST_NAN);
     if (r < m) prologue_vals<KIND>(D, w, r, e.d, e.z, e.c, dn);
   }
   if constexpr (!ONE) {
@@ -181,10 +181,17 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     if (r < m && d == 0.0) zp = 1;
     acc = dd_add(acc, corner_term<KIND>(D, w, r));
   }
-  if (__syncthreads_or(st & ST_NAN)) {   // some slots were never written: compare the inputs themselves
+  if (__syncthreads_or(st & ST_NAN)) {
+    // the poles that are numbers, ranked among themselves, fill the first entries; the
+    // others hold what was there (nothing is solved, so nothing else reads them)
+    int written = 0;
+    for (int r0 = 0; r0 < ms; r0 += PREP_BLOCK) {
+      const int r = r0 + threadIdx.x;
+      written += __syncthreads_count(r < ms && !(w.st[r] & ST_NAN));
+    }
     dup = 0;
-    for (int q = threadIdx.x; q < ms; q += PREP_BLOCK)
-      for (int l = 0; l < ms; ++l) dup |= l != q && key(poles[l]) == key(poles[q]);
+    for (int r = threadIdx.x; r + 1 < written; r += PREP_BLOCK)
+      dup |= sort_key<KIND>(w.ds[r]) == sort_key<KIND>(w.ds[r + 1]);
   }
   if (threadIdx.x == 0) *in_order(w) = down ? 0u : 1u;
   prologue_reduce<KIND, PREP_BLOCK>(D, w, acc, (st & ~ST_NAN) | (dup ? INFO_REDUCIBLE : 0u), zp);
