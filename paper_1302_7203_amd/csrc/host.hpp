@@ -104,11 +104,17 @@ static inline bool large_kernel_lanes(const arrow_handle_s* h, int64_t n) {
 }
 
 // Blocks of the launch that finishes a small problem that re-solve its listed
-// eigenvalues: one a compute unit, and no fewer than let a block of `block` threads
-// ask each of its eigenvalues with a thread of its own.
+// eigenvalues: three a compute unit, which run two at a time.  An eigenvalue each up to
+// three times the compute units; two listed ones in one block run in turn, and with one
+// block a compute unit one such pair in the whole problem held up the launch (graded,
+// values alone, n = 1000: 57.8 us, now 52.7; a launch after the check 53.4).  A block
+// each up to n = 1280 costs the others their dispatch (uniform, n = 1280: 51.0 -> 53.6 us,
+// three a unit 52.4).  And no fewer blocks than let one of `block` threads ask each of its
+// eigenvalues with a thread of its own.
 static inline int finish_redo_blocks(int64_t n, int cus, int block) {
-  const int64_t a = n < cus ? n : cus, b = (n + block - 1) / block;
-  return (int)(a > b ? a : b);
+  const int64_t want = 3 * (int64_t)cus, least = (n + block - 1) / block;
+  const int64_t b = want > least ? want : least;
+  return (int)(n < b ? n : b);
 }
 
 // all launches of one single-problem solve (defined with the single-problem kernels)

@@ -13,5 +13,5 @@ def test_a_thread_per_eigenvalue(cus):
         blocks = emu.finish_redo_blocks(n, cus, BLOCK)
         assert 1 <= blocks <= n
         assert (n + blocks - 1) // blocks <= BLOCK   # the first block's share, the largest
-        if cus * BLOCK >= n:
-            assert blocks == min(n, cus)
+        if n <= 3 * cus:
+            assert blocks == n                       # no listed eigenvalue waits for another
