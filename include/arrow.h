@@ -353,8 +353,9 @@ int arrow_set_default_lanes(arrow_handle_t h, int32_t entries, const int32_t* n_
  *   root (shift, b, root of the inverse), check (K_nu, repairs, norm) and vectors.
  *   The events are stamped by the kernels' own dispatches (no marker packets
  *   between launches): front (up to 16384 poles), root and vectors are their
- *   kernels' durations, sort and check the time between them.  Up to n = 1280 one
- *   kernel does check and vectors, and counts as vectors; without vectors, the
+ *   kernels' durations, sort and check the time between them.  Up to n = 1280 (by
+ *   bisection three times the compute units) one kernel does check and vectors, and
+ *   counts as vectors; without vectors, the
  *   last kernel of the check does.  From n = 4609 while the poles fit a compute
  *   unit's LDS (n to about 20200) root writes most of the vectors itself.  The five sum to the call up to the end of that
  *   kernel.  Needs ARROW_OPT_TIMING set before that call; waits for it to finish.

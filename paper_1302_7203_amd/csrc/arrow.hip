@@ -1007,8 +1007,15 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
     const size_t lds = (hot <= h->lds_max) ? hot : 0;
     launch_root_any<SK>(single_lanes(h, D.n), D, h->opt, st, lds, at(2), at(3));
   }
+  // One launch finishes small problems.  By bisection (ARROW_OPT_ROOT 0) a repair takes
+  // 30 us instead of 10, so there only while every redo block has one eigenvalue: two
+  // listed ones in turn cost more than the launches saved (one block a compute unit,
+  // arrowhead n = 257 129 -> 140 us, DPR1 n = 1000 193 -> 223)
+  const int redo_blocks = finish_redo_blocks(D.n, h->cus, BLOCK);
+  const bool one_finish = D.n <= FIN_MAX && (h->opt.root == ROOT_RATIONAL || redo_blocks == D.n);
   {
-    const VecShape sh = vec_shape(D.n);
+    VecShape sh = vec_shape(D.n);
+    if (!one_finish && sh.rpt < 4) sh = VecShape{4, 4};   // k_vec's smallest
     // 16-byte stores: a complex entry each, or two rows where every column starts on 16 bytes
     const bool pair = pair_rows;
     constexpr int W2 = KIND == KIND_HERM ? 1 : 2;
@@ -1019,8 +1026,7 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
       else if (sh.rpt == 4) { if (pair) go(two(), std::integral_constant<int, 4>()); else go(one(), std::integral_constant<int, 4>()); }
       else { if (pair) go(two(), std::integral_constant<int, 2>()); else go(one(), std::integral_constant<int, 2>()); }
     };
-    if (D.n <= FIN_MAX) {
-      const int redo_blocks = finish_redo_blocks(D.n, h->cus, BLOCK);
+    if (one_finish) {
       const int cols = D.V ? sh.cols : FIN_VALUES;
       const dim3 grid((unsigned)(redo_blocks + (D.n + cols - 1) / cols));
       by_shape([&](auto wd, auto rpt) {
@@ -1061,7 +1067,7 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
       }
     }
   }
-  if (KIND == KIND_ARROW && D.n > FIN_MAX && !D.V)
+  if (KIND == KIND_ARROW && !one_finish && !D.V)
     hipLaunchKernelGGL(k_defl, dim3((unsigned)std::min<int64_t>(D.n - 1, h->cus)), dim3(BLOCK), 0, st, D);
   if (tm) {
     h->ev_set = es;
