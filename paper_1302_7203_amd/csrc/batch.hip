@@ -394,11 +394,15 @@ __global__ __launch_bounds__(STAGE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))
 // problem's list, each listed eigenvalue run by a whole block.  Most problems list
 // nothing, so a block asks `group` turns at once, a lane each, and runs those with
 // work (a block a turn was 10,000 dispatches for the 10,000-problem plan, a turn
-// after the other 110 us of dependent loads).
+// after the other 110 us of dependent loads).  Two wavefronts a SIMD, for which a few
+// registers spill: with one, plans where every problem has a repair took 305 us here
+// instead of 172 (10,000 of n = 16..64; now 185).
 constexpr int REPAIR_BLOCK = 256;
 constexpr int REPAIR_GROUP = 64;   // most turns asked at once: a ballot's
+constexpr int REPAIR_BLOCKS = 8;   // blocks a compute unit
 
-__global__ __launch_bounds__(REPAIR_BLOCK) void k_b_repair(BatchArgs B, Options opt, int per, int group) {
+__global__ __launch_bounds__(REPAIR_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_b_repair(
+    BatchArgs B, Options opt, int per, int group) {
   __shared__ uint64_t work;
   const int64_t turns = (int64_t)B.count * per;
   for (int64_t base = (int64_t)blockIdx.x * group; base < turns; base += (int64_t)gridDim.x * group) {
@@ -761,8 +765,9 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   b->check_blocks = (int)std::min<int64_t>(8 * (int64_t)h->cus, citem_blocks);
   b->remedy_blocks = (int)std::min<int64_t>(4 * (int64_t)h->cus, (L.pairs + STAGE_BLOCK / WAVE - 1) / (STAGE_BLOCK / WAVE));
   const int64_t turns = count * b->repair_per;
-  b->repair_group = (int)std::min<int64_t>(REPAIR_GROUP, (turns + 4 * (int64_t)h->cus - 1) / (4 * (int64_t)h->cus));
-  b->repair_blocks = (int)std::min<int64_t>(4 * (int64_t)h->cus, (turns + b->repair_group - 1) / b->repair_group);
+  const int64_t rblocks = REPAIR_BLOCKS * (int64_t)h->cus;
+  b->repair_group = (int)std::min<int64_t>(REPAIR_GROUP, (turns + rblocks - 1) / rblocks);
+  b->repair_blocks = (int)std::min<int64_t>(rblocks, (turns + b->repair_group - 1) / b->repair_group);
   if ((flags & ARROW_BATCH_TIMING) && !(flags & ARROW_BATCH_GRAPH)) {
     b->ev_made = 1;
     for (int e = 0; e < 10; ++e)
