@@ -200,13 +200,7 @@ constexpr int ROOT_STAGE = AHD_ROOT_STAGE;
 
 // Root items are taken from the queue a chunk at a time (one atomic per chunk):
 // the queue counter is a single L2 address, and with one atomic per item its
-// serialised updates (a few ns each over ~10^6 items) set the stage's time.  A
-// plan with fewer than CHUNK_FROM items per resident wavefront takes them one by
-// one: an item is 100 us and more of a wavefront's time at n = 2048, and two to a
-// wavefront leave half of the wavefronts idle (32 problems up to n = 2048: 277 us
-// by twos).
-constexpr int ROOT_CHUNK = 2;
-constexpr int CHUNK_FROM = 8;
+// serialised updates (18 ns each) set the stage's time: root_chunk (host.hpp).
 
 // at least ROOT_WAVES wavefronts per SIMD: the pole loads come from L2 and need company to hide
 #ifndef AHD_ROOT_WAVES
@@ -759,7 +753,7 @@ int arrow_batch_create(arrow_handle_t h, int64_t count, const arrow_desc_t* desc
   const int64_t want = (int64_t)h->cus * 4 * ROOT_WAVES * WAVE / STAGE_BLOCK;
   const int64_t need = ((int64_t)items * WAVE + STAGE_BLOCK - 1) / STAGE_BLOCK;
   b->persistent_blocks = (int)std::max<int64_t>(1, std::min(want, need));
-  A.chunk = items >= CHUNK_FROM * want * (STAGE_BLOCK / WAVE) ? ROOT_CHUNK : 1;
+  A.chunk = root_chunk(items - shared, want * (STAGE_BLOCK / WAVE));
   // one item a wavefront, eight blocks a compute unit at most; remedies and repairs are few
   const int64_t citem_blocks = (citems + STAGE_BLOCK / WAVE - 1) / (STAGE_BLOCK / WAVE);
   b->check_blocks = (int)std::min<int64_t>(8 * (int64_t)h->cus, citem_blocks);

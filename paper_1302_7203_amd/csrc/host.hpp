@@ -117,6 +117,14 @@ static inline int finish_redo_blocks(int64_t n, int cus, int block) {
   return (int)(n < b ? n : b);
 }
 
+// Root items of a batched plan that a wavefront takes from the queue at a time, of
+// `items` beside the shared ones, for `waves` resident wavefronts: two, unless that
+// leaves wavefronts without any, below one and a half a wavefront.  By ones, 10,000
+// problems of n = 16..64 (6.4 items a wavefront) take 433 us, by twos 320; 5000 (3.2)
+// 253 and 198; 1200 of n = 64..128 (1.8) 180 and 152; but 300 of n = 128..512 (1.3) 174
+// and 207, 150 of n = 256..600 (0.9) 163 and 211.
+static inline int root_chunk(int64_t items, int64_t waves) { return 2 * items < 3 * waves ? 1 : 2; }
+
 // all launches of one single-problem solve (defined with the single-problem kernels)
 int launch_single(arrow_handle_t h, const ahd::ProbDesc& D);
 

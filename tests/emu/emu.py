@@ -37,6 +37,8 @@ def _load():
         L.emu_solve.restype = ctypes.c_int
         L.emu_finish_redo_blocks.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
         L.emu_finish_redo_blocks.restype = ctypes.c_int
+        L.emu_root_chunk.argtypes = [ctypes.c_int64, ctypes.c_int64]
+        L.emu_root_chunk.restype = ctypes.c_int
         L.emu_set_batch_check.argtypes = [ctypes.c_int]
         L.emu_set_batch_check.restype = None
         _lib = L
@@ -62,6 +64,11 @@ def set_finish_check(on: bool):
 def finish_redo_blocks(n: int, cus: int, block: int) -> int:
     """Blocks that re-solve the listed eigenvalues of a small single problem."""
     return _load().emu_finish_redo_blocks(n, cus, block)
+
+
+def root_chunk(items: int, waves: int) -> int:
+    """Root items of a plan that a wavefront takes at a time."""
+    return _load().emu_root_chunk(items, waves)
 
 
 def solve(kind, d, z, scalar, vectors=True, tau_nu=100.0, tau_zero=10.0, fp64_b=0, remedies=1, root=1, tau_b=0.0):

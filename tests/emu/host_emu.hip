@@ -128,6 +128,8 @@ extern "C" void emu_set_batch_check(int on) { g_batch_check = on; }
 
 extern "C" int emu_finish_redo_blocks(int64_t n, int cus, int block) { return finish_redo_blocks(n, cus, block); }
 
+extern "C" int emu_root_chunk(int64_t items, int64_t waves) { return root_chunk(items, waves); }
+
 extern "C" int emu_solve(int kind, int64_t n, const double* d, const double* z, double scalar, double* lam,
                          double* V, double* U, double* shift, double* mu, uint32_t* info, double tau_nu,
                          double tau_zero, int fp64_b, int remedies, double* kb, int root, int32_t* cnt,
