@@ -59,6 +59,23 @@ struct DeviceGuard {
   }
 };
 
+// Zeros in the header of a new workspace, where the sort's completion count starts at 0
+// (each call leaves it there).  On a stream of its own while the caller's is captured: a
+// first call may be (relaxed capture mode allows the allocation), and neither a wait nor
+// a memset belongs in its graph.
+static inline bool clear_header(double* ws, hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  hipStream_t own = nullptr;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone) {
+    if (hipStreamCreateWithFlags(&own, hipStreamNonBlocking) != hipSuccess) return false;
+    stream = own;
+  }
+  const bool ok = hipMemsetAsync(ws, 0, 16 * sizeof(double), stream) == hipSuccess &&
+                  hipStreamSynchronize(stream) == hipSuccess;
+  if (own) (void)hipStreamDestroy(own);
+  return ok;
+}
+
 static inline int ensure_ws(arrow_handle_t h, size_t doubles) {
   if (doubles <= h->ws_cap) return ARROW_OK;
   if (h->ws) {
@@ -71,9 +88,7 @@ static inline int ensure_ws(arrow_handle_t h, size_t doubles) {
     h->ws = nullptr;
     return ARROW_ERR_NOMEM;
   }
-  // the sort's completion count starts at 0; each call leaves it there
-  if (hipMemsetAsync(h->ws, 0, 16 * sizeof(double), h->stream) != hipSuccess ||
-      hipStreamSynchronize(h->stream) != hipSuccess) {
+  if (!clear_header(h->ws, h->stream)) {
     (void)hipFree(h->ws);
     h->ws = nullptr;
     return ARROW_ERR_HIP;
