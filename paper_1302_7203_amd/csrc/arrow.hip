@@ -1128,7 +1128,6 @@ int arrow_create(arrow_handle_t* h, int device) {
   p->device = device;
   p->stream = nullptr;
   p->opt.tau_nu = 100.0;
-  p->opt.check_lanes = 4;
   p->opt.tau_zero = 10.0;
   p->opt.fp64_b = 0;
   p->opt.tau_b = 0.0;
@@ -1196,11 +1195,9 @@ int arrow_set_option(arrow_handle_t h, int option, double value) {
       if (value != 0.0 && value != 1.0) return -3;
       h->opt.root = (int)value;
       return ARROW_OK;
-    case ARROW_OPT_CHECK_LANES: {
+    case ARROW_OPT_CHECK_LANES: {   // accepted without effect
       const int g = (int)value;
-      if (!((double)g == value && (g == 0 || (g >= 4 && g <= 64 && (g & (g - 1)) == 0)))) return -3;
-      h->opt.check_lanes = g;
-      return ARROW_OK;
+      return ((double)g == value && (g == 0 || (g >= 4 && g <= 64 && (g & (g - 1)) == 0))) ? ARROW_OK : -3;
     }
     case ARROW_OPT_TIMING:
       if (value != 0.0 && !h->ev_made) {

@@ -151,7 +151,7 @@ extern "C" int emu_solve(int kind, int64_t n, const double* d, const double* z, 
   D.mu = mu;
   D.info = info;
   D.ws = ws.data();
-  Options opt{tau_nu, tau_zero, fp64_b, remedies, root, tau_b, 0};
+  Options opt{tau_nu, tau_zero, fp64_b, remedies, root, tau_b};
   if (kind == KIND_ARROW) run<KIND_ARROW>(D, opt, U);
   else if (kind == KIND_DPR1) run<KIND_DPR1>(D, opt, U);
   else if (kind == KIND_HERM) run<KIND_HERM>(D, opt, U);
