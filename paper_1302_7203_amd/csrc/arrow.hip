@@ -156,7 +156,7 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     // behind the barrier one thread releases the block's entries at device scope
     // (a write-back of the L2 a wavefront, so one is enough) and counts the block
     // in; the last block acquires.  The count wraps to 0, and a later launch of every
-    // call (k_finish, k_repair) stores 0 as well: calls that overlapped in one workspace
+    // call (k_finish, k_check, k_check_edges) stores 0 as well: calls that overlapped in one workspace
     // may leave another value, and the first one ordered behind them must find 0
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -548,6 +548,7 @@ template <int KIND>
 __global__ __launch_bounds__(CHECK_BLOCK) void k_check(ProbDesc D, Options opt) {
   const int k = (int)(blockIdx.x * CHECK_BLOCK + threadIdx.x);
   if (k >= D.n) return;
+  if (k == 0) *sort_done(ws_view(D.ws, D.n)) = 0u;   // for the next call
   if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0)) defer_repair(ws_view(D.ws, D.n), D.n, k, 0);
 }
 
@@ -559,7 +560,6 @@ __global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt
   extern __shared__ double lds[];
   const Ws w = ws_view(D.ws, D.n);
   const uint32_t count = min(*repair_count(w), (uint32_t)D.n);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *sort_done(w) = 0u;   // for the next call
   if (blockIdx.x >= count) return;
   if constexpr (STAGE) stage_hot(D, lds);
   const uint32_t* list = repair_list(w, D.n);
@@ -844,6 +844,7 @@ template <int KIND>
 __global__ __launch_bounds__(CHECK_BLOCK) void k_check_edges(ProbDesc D, Options opt, BigTail T) {
   const int e = (int)(blockIdx.x * CHECK_BLOCK + threadIdx.x);
   if (e >= 2 * T.blocks) return;
+  if (e == 0) *sort_done(ws_view(D.ws, D.n)) = 0u;   // for the next call
   const int k = T.edge(e, D.n);
   if (k < 0) return;
   if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0)) defer_repair(ws_view(D.ws, D.n), D.n, k, 0);
