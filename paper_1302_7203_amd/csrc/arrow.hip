@@ -11,9 +11,10 @@
 //   k_finish    per eigenvalue: K_nu test (Algorithm 5), repairs (Remarks 1-2, DPR1
 //               re-measure), norm, then its eigenvector, streamed to HBM
 //               (eq. eigenvecAi, Algorithm 4; complex for a Hermitian arrowhead, Sec. 6.1).
-//               Above FIN_MAX k_check, k_repair and k_vec take its place, with the
-//               eigenpairs a reducible arrowhead deflated (Sec. 1) in k_vec's launch,
-//               without vectors in one of their own (k_defl)
+//               Above FIN_MAX (by bisection three times the compute units) k_check,
+//               k_repair and k_vec take its place, with the eigenpairs a reducible
+//               arrowhead deflated (Sec. 1) in k_vec's launch, without vectors in one
+//               of their own (k_defl)
 // k_root gives G lanes of a wavefront to each eigenvalue (G = 64: one
 // wavefront per eigenvalue); the vectors are bound by the n^2 FP64 stores.
 
@@ -362,10 +363,11 @@ __global__ __launch_bounds__(ROOT_BLOCK) void k_root(ProbDesc D, Options opt) {
 // eigenvalues: test and outputs, one lane each, then the columns that are final,
 // BLOCK * RPT rows at a time with the rows' data in registers.  The repairs are
 // left to the redo blocks, first in the grid: block b asks of k = b, b +
-// redo_blocks, ..., re-solves those on all its lanes from arrays staged in LDS and
-// writes their columns, so a repair's chain of passes (10 us) runs beside the
-// other blocks instead of between two launches (n = 512: 12 us against 20 us for
-// check, repair and vectors; n = 1025 complex 20 us against 23 us).
+// redo_blocks, ... (one each up to three times the compute units, finish_redo_blocks),
+// re-solves those on all its lanes from arrays staged in LDS and writes their columns,
+// so a repair's chain of passes (10 us) runs beside the other blocks instead of between
+// two launches (n = 512: 11.6 us against 20 us for check, repair and vectors; n = 1025
+// complex 16 us against 23 us).
 //
 // Above, a launch each (k_check, k_repair, k_vec): the redo blocks would reserve
 // 16 n bytes of LDS in every block of the launch, and clusters of listed

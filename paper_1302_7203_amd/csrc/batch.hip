@@ -207,7 +207,7 @@ constexpr int ROOT_STAGE = AHD_ROOT_STAGE;
 #define AHD_ROOT_WAVES 4
 #endif
 constexpr int ROOT_WAVES = AHD_ROOT_WAVES;
-//
+
 // Items [0, B.shared_items), the orders above 640 that a wavefront's own slice holds
 // in part or not at all: a block takes four consecutive items, a wavefront each, and
 // stages the first one's problem in the LDS of all four slices (both arrays up to
