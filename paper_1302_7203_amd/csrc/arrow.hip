@@ -13,8 +13,8 @@
 //               (eq. eigenvecAi, Algorithm 4; complex for a Hermitian arrowhead, Sec. 6.1).
 //               Above FIN_MAX (by bisection three times the compute units) k_check,
 //               k_repair and k_vec take its place, with the eigenpairs a reducible
-//               arrowhead deflated (Sec. 1) in k_vec's launch, without vectors in one
-//               of their own (k_defl)
+//               arrowhead deflated (Sec. 1) in k_vec's launch, without vectors in
+//               k_repair's
 // k_root gives G lanes of a wavefront to each eigenvalue (G = 64: one
 // wavefront per eigenvalue); the vectors are bound by the n^2 FP64 stores.
 
@@ -68,7 +68,7 @@ constexpr int PREP_BLOCK = 1024;
 constexpr int PREP_WAVES = PREP_BLOCK / 64;
 constexpr int PREP_ONE = 256;     // poles one block ranks alone: 64 comparisons a lane
 constexpr int PREP_MAX = 16384;   // the blocks' order checks read n^2 / 64 keys from the L2
-constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (it has no rank and no sorted entry)
+constexpr uint32_t ST_NAN = 1u << 30;   // input status: a pole that is not a number (it has no rank)
 
 // blocks of the sort that are done: 0 between calls
 __host__ __device__ inline uint32_t* sort_done(const Ws& w) { return (uint32_t*)(w.hdr + 7); }
@@ -148,17 +148,19 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     r = 0;
     for (int q = 0; q < shares; ++q) r += part[q * groups + grp][lane];
   }
-  if (has) w.st[j] = input_status_vals<KIND>(dj, re, im, false) | (kj == kj ? 0u : ST_NAN);
-  if (has && kj == kj) {   // r < ms: the other keys in front of j's
+  if (kj != kj) r = ms - 1;   // behind every number: those fill the first entries
+  if (has) {   // r < ms: the other keys in front of j's
     const SortedEntry e = put_sorted_vals<KIND>(w, r, j, (KIND == KIND_DPR1 && D.neg) ? -dj : dj, re, im);
+    w.st[j] = input_status_vals<KIND>(dj, re, im, false) | (kj == kj ? 0u : ST_NAN);
     if (r < m) prologue_vals<KIND>(D, w, r, e.d, e.z, e.c, dn);
   }
   if constexpr (!ONE) {
     // behind the barrier one thread releases the block's entries at device scope
     // (a write-back of the L2 a wavefront, so one is enough) and counts the block
     // in; the last block acquires.  The count wraps to 0, and a later launch of every
-    // call (k_finish, k_check, k_check_edges) stores 0 as well: calls that overlapped in one workspace
-    // may leave another value, and the first one ordered behind them must find 0
+    // call (k_finish, k_check, k_check_edges) stores 0 as well: calls that overlapped
+    // in one workspace may leave another value, and the first one ordered behind them
+    // must find 0
     __syncthreads();
     if (threadIdx.x == 0) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -183,8 +185,8 @@ __global__ __launch_bounds__(PREP_BLOCK) void k_prep(ProbDesc D, const double* _
     acc = dd_add(acc, corner_term<KIND>(D, w, r));
   }
   if (__syncthreads_or(st & ST_NAN)) {
-    // the poles that are numbers, ranked among themselves, fill the first entries; the
-    // others hold what was there (nothing is solved, so nothing else reads them)
+    // the poles that are numbers, ranked among themselves, fill the first entries; most
+    // of the others hold what was there (nothing is solved, so nothing else reads them)
     int written = 0;
     for (int r0 = 0; r0 < ms; r0 += PREP_BLOCK) {
       const int r = r0 + threadIdx.x;
@@ -479,7 +481,8 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
   const bool redo = (int)blockIdx.x < redo_blocks;
   const int step = redo ? redo_blocks : 1;
   const int k0 = redo ? (int)blockIdx.x : ((int)blockIdx.x - redo_blocks) * cols;
-  const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);   // at most BLOCK (finish_redo_blocks), cols
+  // at most BLOCK (finish_redo_blocks), at most cols
+  const int mine = redo ? (D.n - k0 + step - 1) / step : min(D.n - k0, cols);
   if (t == 0) L.redo_count = 0;
   if (blockIdx.x == 0 && t == 0) *sort_done(w) = 0u;   // for the next call
   __syncthreads();
@@ -524,14 +527,14 @@ __global__ __launch_bounds__(BLOCK) void k_finish(ProbDesc D, Options opt, int r
       int above = 0;
 #pragma unroll
       for (int q = 0; q < FIN_MAX / BLOCK; ++q) above += __syncthreads_count(d[q] >= v);
-      const int col = s + deflated_above<SK>(D, opt, w, v, above, [&](int k) {
-        if (!staged) {
-          stage_hot(D, lds);
-          staged = true;
-        }
-        check_body<SK, BLOCK, true>(D, opt, k, t, lds, lds + sorted_count(D));
+      const bool solve = check_body<SK, 1, false, DEFER_BLOCK>(D, opt, above, 0, nullptr, nullptr, false);
+      if (solve) {
+        if (!staged) stage_hot(D, lds);
+        staged = true;
+        check_body<SK, BLOCK, true>(D, opt, above, t, lds, lds + sorted_count(D));
         __syncthreads();
-      });
+      }
+      const int col = s + above + (rival_key<SK>(w, above, solve) >= v ? 1 : 0);
       if (t == 0) place_deflated_at(D, w, s, col);
       if (D.V) {
         double* vc = D.V + (size_t)col * (size_t)D.ldv;
@@ -554,29 +557,58 @@ __global__ __launch_bounds__(CHECK_BLOCK) void k_check(ProbDesc D, Options opt) 
   if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0)) defer_repair(ws_view(D.ws, D.n), D.n, k, 0);
 }
 
-// The listed eigenvalues, a block each; blocks beyond the list's length return.
+// The listed eigenvalues, a block each; blocks beyond the list's length return.  Without
+// vectors also the deflated pairs of a reducible arrowhead, each of which needs one final
+// eigenvalue (deflated_rival): a thread places those whose rival the check finished, and
+// the block that re-solves a listed one places its pairs.  A launch behind this one for
+// them costs every call (n = 1281, values alone: 53.7 -> 52.3 us,
+// graded n = 4096 with a quarter of the shaft zero 111.8 -> 106.0).
 constexpr int REPAIR_BLOCK = 256;
 
 template <int KIND, bool STAGE>
 __global__ __launch_bounds__(REPAIR_BLOCK) void k_repair(ProbDesc D, Options opt) {
   extern __shared__ double lds[];
+  __shared__ int first[REPAIR_BLOCK], past[REPAIR_BLOCK];   // the pairs of the block's listed eigenvalues
   const Ws w = ws_view(D.ws, D.n);
   const uint32_t count = min(*repair_count(w), (uint32_t)D.n);
-  if (blockIdx.x >= count) return;
+  const uint32_t pairs = (KIND == KIND_ARROW && !D.V) ? (uint32_t)deflated_count(w) : 0u;
+  const uint32_t step = gridDim.x, total = max(count, pairs);
+  if (blockIdx.x >= total) return;
   if constexpr (STAGE) stage_hot(D, lds);
   const uint32_t* list = repair_list(w, D.n);
-  for (uint32_t q = blockIdx.x; q < count; q += gridDim.x) {
-    const int k = (int)list[q];
-    if (k < 0 || k >= D.n) continue;
-    check_body<KIND, REPAIR_BLOCK, STAGE>(D, opt, k, threadIdx.x, lds, lds + sorted_count(D));
+  for (uint64_t e0 = blockIdx.x; e0 < total; e0 += (uint64_t)REPAIR_BLOCK * step) {   // e0 + t step: thread t's
+    if (KIND == KIND_ARROW && pairs > 0u) {
+      const uint64_t e = e0 + (uint64_t)threadIdx.x * step;
+      if (e < count) {
+        rival_pairs(w, (int)list[e], &first[threadIdx.x], &past[threadIdx.x]);
+      }
+      if (e < pairs) {
+        const int s = (int)e, k = deflated_rival(w, w.dv[s]);
+        if (!check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, k, 0, nullptr, nullptr, false))
+          place_deflated_at(D, w, s, s + k + (rival_key<KIND>(w, k, false) >= w.dv[s] ? 1 : 0));
+      }
+      __syncthreads();
+    }
+    for (uint32_t q = 0; q < (uint32_t)REPAIR_BLOCK && e0 + (uint64_t)q * step < count; ++q) {
+      const int k = (int)list[e0 + (uint64_t)q * step];
+      if (k < 0 || k >= D.n) continue;
+      check_body<KIND, REPAIR_BLOCK, STAGE>(D, opt, k, threadIdx.x, lds, lds + sorted_count(D));
+      if (KIND == KIND_ARROW && pairs > 0u) {
+        __syncthreads();
+        const double key = rival_key<KIND>(w, k, true);
+        for (int s = first[q] + (int)threadIdx.x; s < past[q]; s += REPAIR_BLOCK)
+          place_deflated_at(D, w, s, s + k + (key >= w.dv[s] ? 1 : 0));
+      }
+    }
+    if (KIND == KIND_ARROW && pairs > 0u) __syncthreads();
   }
 }
 
 // The deflated eigenpairs of a reducible arrowhead (n > FIN_MAX), by `blocks` blocks in
 // turn: placed among the solved ones, whose values are final, and their vectors.  The
-// columns are nobody else's, so with vectors these blocks ride behind the others of the
-// vector launch; a launch of their own (k_defl, without vectors) takes 4.6 us also for
-// the usual irreducible input, where every block returns at once.
+// columns are nobody else's, so these blocks ride behind the others of the vector
+// launch; a launch of their own takes 4.6 us also for the usual irreducible input,
+// where every block returns at once.
 __device__ inline void defl_pairs(const ProbDesc& D, int b, int blocks) {
   __shared__ int col;
   const Ws w = ws_view(D.ws, D.n);
@@ -584,11 +616,9 @@ __device__ inline void defl_pairs(const ProbDesc& D, int b, int blocks) {
   for (int s = b; s < nd; s += blocks) {
     if (threadIdx.x == 0) col = place_deflated(D, w, s);
     __syncthreads();
-    if (D.V) {
-      double* vc = D.V + (size_t)col * (size_t)D.ldv;
-      for (int r = threadIdx.x; r < D.n; r += BLOCK)
-        __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
-    }
+    double* vc = D.V + (size_t)col * (size_t)D.ldv;
+    for (int r = threadIdx.x; r < D.n; r += BLOCK)
+      __builtin_nontemporal_store(r < D.n - 1 ? deflated_entry(w, s, w.iperm[r], D.z[r]) : 0.0, vc + r);
     __syncthreads();
   }
 }
@@ -886,8 +916,6 @@ __global__ __launch_bounds__(BLOCK) void k_vec_tail(ProbDesc D, int row_tiles, B
   }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_defl(ProbDesc D) { defl_pairs(D, (int)blockIdx.x, (int)gridDim.x); }
-
 // ---------------------------------------------------------------------------
 // host side
 
@@ -992,10 +1020,10 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
   // and the caller did not ask for another number of lanes
   const int each = (int)std::max<int64_t>(BIG_EACH, (D.n + h->cus - 1) / h->cus);
   const size_t poles = (size_t)ms * sizeof(double), extra = big_lds(each) + 1024;   // and a little static LDS
-  // Not where the caller takes the shift pairs or either half of them: the shift of Remark 2(b) is formed from
-  // the first pass's mu, of which an ill-conditioned eigenvalue has few digits, and the
-  // pair's mu shows all of them (20 decades, n = 6000: 5e-9 between two lane counts, the
-  // eigenvalues equal).  The pairs stay those of the tuned lane count.
+  // Not where the caller takes the shift pairs or either half of them: the shift of
+  // Remark 2(b) is formed from the first pass's mu, of which an ill-conditioned eigenvalue
+  // has few digits, and the pair's mu shows all of them (20 decades, n = 6000: 5e-9 between
+  // two lane counts, the eigenvalues equal).  The pairs stay those of the tuned lane count.
   const bool big = D.n > BIG_MIN && large_kernel_lanes(h, D.n) && !D.shift && !D.mu && poles + extra <= h->lds_max;
   const BigTail tail{each, (D.n + each - 1) / each};
   const bool hot_both = hot + extra <= h->lds_max;
@@ -1070,8 +1098,6 @@ static int launch_problem(arrow_handle_t h, const ProbDesc& D) {
       }
     }
   }
-  if (KIND == KIND_ARROW && !one_finish && !D.V)
-    hipLaunchKernelGGL(k_defl, dim3((unsigned)std::min<int64_t>(D.n - 1, h->cus)), dim3(BLOCK), 0, st, D);
   if (tm) {
     h->ev_set = es;
     h->timed_calls = std::min(h->timed_calls + 1, 2);

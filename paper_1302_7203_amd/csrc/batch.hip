@@ -200,7 +200,7 @@ constexpr int ROOT_STAGE = AHD_ROOT_STAGE;
 
 // Root items are taken from the queue a chunk at a time (one atomic per chunk):
 // the queue counter is a single L2 address, and with one atomic per item its
-// serialised updates (18 ns each) set the stage's time: root_chunk (host.hpp).
+// serialised updates (18 ns each) set the stage's time.  root_chunk says how many.
 
 // at least ROOT_WAVES wavefronts per SIMD: the pole loads come from L2 and need company to hide
 #ifndef AHD_ROOT_WAVES

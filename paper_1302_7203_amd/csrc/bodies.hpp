@@ -379,9 +379,9 @@ __host__ __device__ inline double deflated_entry(const Ws& w, int s, int j, doub
 // it lies in exact arithmetic: so the keys descend whatever an eigenvalue's
 // accuracy (remedies off, an extreme tau_nu), both sides decide by the same keys,
 // and the columns are a permutation.  An accurate lambda_k is its own key.
-__host__ __device__ inline double merge_key(const Ws& w, int k, double lam) {
-  if (k < reduced_m(w)) lam = fmax(lam, w.ds[k]);
-  if (k > 0) lam = fmin(lam, w.ds[k - 1]);
+__host__ __device__ inline double merge_key(const double* ds, int m, int k, double lam) {
+  if (k < m) lam = fmax(lam, ds[k]);
+  if (k > 0) lam = fmin(lam, ds[k - 1]);
   return lam;
 }
 
@@ -807,7 +807,7 @@ __host__ __device__ __forceinline__ bool check_body(const ProbDesc& D, const Opt
     if constexpr (KIND == KIND_ARROW) {
       const int nd = deflated_count(w);
       if (nd > 0) {
-        const double key = merge_key(w, k, lam);
+        const double key = merge_key(P.ds, m, k, lam);
         col = k + count_above(w.dv, nd, key, false);
         w.lr[k] = key;
         w.cm[col] = -1;
@@ -837,23 +837,25 @@ __host__ __device__ __forceinline__ bool check_body(const ProbDesc& D, const Opt
   return false;
 }
 
-// #{key >= v} of place_deflated for a deflated value v, before the reduced
-// eigenvalues are all final: those of the reduced poles at or above v are above
-// it and those of the poles below v but the first are below, whatever their
-// values, so only eigenvalue b = #{reduced poles >= v} is compared.  Its first
-// pass is final unless the check asks for a repair, which `resolve(b)` then runs
-// (check_body with DEFER_NONE, and a barrier where several threads share the work).
-template <int KIND, class F>
-__host__ __device__ inline int deflated_above(const ProbDesc& D, const Options& opt, const Ws& w, double v, int b,
-                                              F&& resolve) {
-  double key;
-  if (check_body<KIND, 1, false, DEFER_BLOCK>(D, opt, b, 0, nullptr, nullptr, false)) {
-    resolve(b);
-    key = w.lr[b];
-  } else {
-    key = merge_key(w, b, dd_to_d(dd_add_d(dd_add_d(pval_dd<KIND>(w.pv1[b]), 0.0), w.mu1[b])));
-  }
-  return b + (key >= v ? 1 : 0);
+// place_deflated's count #{key >= v} for a deflated value v, before the reduced
+// eigenvalues are all final: those of the reduced poles at or above v are above it and
+// those of the poles below v but the first are below, whatever their values, so only the
+// eigenvalue b = deflated_rival, b = #{reduced poles >= v}, is compared, and the count is
+// b + (its key >= v).  Its first pass is final unless the check asks for a repair
+// (check_body, DEFER_BLOCK, commit = false), which the caller then runs first.
+__host__ __device__ inline int deflated_rival(const Ws& w, double v) { return count_above(w.ds, reduced_m(w), v, true); }
+
+// the pairs [*first, *past) whose rival is eigenvalue k
+__host__ __device__ inline void rival_pairs(const Ws& w, int k, int* first, int* past) {
+  const int nd = deflated_count(w);
+  *first = k > 0 ? count_above(w.dv, nd, w.ds[k - 1], false) : 0;
+  *past = k < reduced_m(w) ? count_above(w.dv, nd, w.ds[k], false) : nd;
+}
+
+template <int KIND>
+__host__ __device__ inline double rival_key(const Ws& w, int b, bool solved) {
+  if (solved) return w.lr[b];
+  return merge_key(w.ds, reduced_m(w), b, dd_to_d(dd_add_d(dd_add_d(pval_dd<KIND>(w.pv1[b]), 0.0), w.mu1[b])));
 }
 
 // ---------------------------------------------------------------------------

@@ -122,7 +122,7 @@ static inline bool large_kernel_lanes(const arrow_handle_s* h, int64_t n) {
 // eigenvalues: three a compute unit, which run two at a time.  An eigenvalue each up to
 // three times the compute units; two listed ones in one block run in turn, and with one
 // block a compute unit one such pair in the whole problem held up the launch (graded,
-// values alone, n = 1000: 57.8 us, now 52.7; a launch after the check 53.4).  A block
+// values alone, n = 1000: 57.5 us, now 52.3; as launches of their own 53.4).  A block
 // each up to n = 1280 costs the others their dispatch (uniform, n = 1280: 51.0 -> 53.6 us,
 // three a unit 52.4).  And no fewer blocks than let one of `block` threads ask each of its
 // eigenvalues with a thread of its own.

@@ -78,9 +78,17 @@ static void run(ProbDesc D, const Options& opt, double* U) {
     for (int k = 0; k < D.n; ++k)
       if (check_body<SK, 1, false, DEFER_BLOCK>(D, opt, k, 0)) again.push_back(k);
     if constexpr (KIND == KIND_ARROW) {
-      for (int s = 0; s < nd; ++s)
-        place_deflated_at(D, w, s, s + deflated_above<SK>(D, opt, w, w.dv[s], count_above(w.ds, reduced_m(w), w.dv[s], true),
-                                                          [&](int k) { check_body<SK, 1>(D, opt, k, 0); }));
+      for (int s = 0; s < nd; ++s) {
+        const int b = deflated_rival(w, w.dv[s]);
+        int first, past;
+        for (int k = 0; k <= reduced_m(w); ++k) {   // pair s is among its rival's, and no other's
+          rival_pairs(w, k, &first, &past);
+          if ((first <= s && s < past) != (k == b)) abort();
+        }
+        const bool solve = check_body<SK, 1, false, DEFER_BLOCK>(D, opt, b, 0, nullptr, nullptr, false);
+        if (solve) check_body<SK, 1>(D, opt, b, 0);
+        place_deflated_at(D, w, s, s + b + (rival_key<SK>(w, b, solve) >= w.dv[s] ? 1 : 0));
+      }
       placed = true;
     }
     for (int k : again) check_body<SK, 1>(D, opt, k, 0);

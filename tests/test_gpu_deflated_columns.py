@@ -72,6 +72,32 @@ def test_larger_single_solves(n, oracle_lib):
         _check(q, out.lam.cpu().numpy(), out.V.cpu().numpy(), out.info.cpu().numpy(), f"graded {n}" + more)
 
 
+@pytest.mark.parametrize("n", [1281, 1500, 3001, 4800])
+def test_larger_without_vectors(n, oracle_lib):
+    """The launch of the repairs places the pairs, those of a listed eigenvalue by its block: more
+    pairs than a block has threads between two poles, and none at all."""
+    import torch
+    rng = np.random.default_rng(n)
+    pr = W.graded_arrow(n - 700, rng, clusters=n // 14)
+    out = _solve(pr, vectors=False)
+    listed = np.nonzero(out.info.cpu().numpy() & 6)[0]
+    d = np.sort(pr.d)[::-1]
+    lam = out.lam.cpu().numpy()
+    # 600 equal rows without shaft between the poles around a listed eigenvalue, 99 on other poles
+    gaps = [(d[k - 1], d[k], lam[k]) for k in listed if 0 < k < d.size and 0.5 * (d[k - 1] + d[k]) not in (d[k - 1], d[k])]
+    hi, lo, at = max(gaps, key=lambda g: (g[0] - g[1]) / abs(g[2]))
+    for v in (0.5 * (hi + at), 0.5 * (at + lo), hi):
+        q = C._with_rows(pr.d, pr.z, pr.scalar, np.concatenate([np.full(600, v), rng.choice(d, 99, replace=False)]))
+        p = rng.permutation(q.d.size)
+        q = W.Problem(q.kind, q.n, q.d[p], q.z[p], q.scalar)
+        full, vals = _solve(q), _solve(q, vectors=False)
+        assert torch.equal(full.lam, vals.lam) and torch.equal(full.info, vals.info)
+        _check(q, vals.lam.cpu().numpy(), full.V.cpu().numpy(), vals.info.cpu().numpy(), f"{n}, {v}")
+    for _, q in _widened(pr):
+        full, vals = _solve(q), _solve(q, vectors=False)
+        assert torch.equal(full.lam, vals.lam) and torch.equal(full.info, vals.info)
+
+
 def test_plan(oracle_lib):
     import torch
     from paper_1302_7203_amd import batch
