@@ -429,14 +429,15 @@ __device__ inline void finish_rows(const ProbDesc& D, int rt, int nc, const FinS
       } else if constexpr (W == 1) {
         const double v = vec_entry<KIND>(dr[q], num[q], r == n - 1, pv, s, mu, inrm);
         __builtin_nontemporal_store(v, vc + r);
-        if (KIND == KIND_SVD && uc) __builtin_nontemporal_store(svd_left(D, sigma, v, r), uc + r);
+        if (KIND == KIND_SVD && uc) __builtin_nontemporal_store(svd_left_d(D, sigma, v, r == n - 1, dr[q]), uc + r);
       } else {
         const double v0 = vec_entry<KIND>(dr[2 * q], num[2 * q], false, pv, s, mu, inrm);
         const double v1 = vec_entry<KIND>(dr[2 * q + 1], num[2 * q + 1], r + 1 == n - 1, pv, s, mu, inrm);
         const v2d vv = {v0, v1};
         __builtin_nontemporal_store(vv, (v2d*)(vc + r));
         if (KIND == KIND_SVD && uc) {
-          const v2d uu = {svd_left(D, sigma, v0, r), svd_left(D, sigma, v1, r + 1)};
+          const v2d uu = {svd_left_d(D, sigma, v0, false, dr[2 * q]),
+                          svd_left_d(D, sigma, v1, r + 1 == n - 1, dr[2 * q + 1])};
           __builtin_nontemporal_store(uu, (v2d*)(uc + r));
         }
       }

@@ -908,6 +908,11 @@ __host__ __device__ inline void vec_entry_c(double dr, double zr, double zi, boo
 
 // SVD left vector entry from the right vector entry v_r: u_j = sigma v_j / d_j,
 // u_n = alpha v_n / sigma
+// (d = d_j, not used for the last entry)
+__host__ __device__ inline double svd_left_d(const ProbDesc& D, double sigma, double v, bool last, double d) {
+  return last ? D.scalar * v / sigma : sigma * v / d;
+}
+
 __host__ __device__ inline double svd_left(const ProbDesc& D, double sigma, double v, int r) {
   return (r == D.n - 1) ? D.scalar * v / sigma : sigma * v / D.d[r];
 }
